@@ -16,10 +16,21 @@
 //
 // Tiling for gfx950: 512 threads = 8 wave64s in a 2x4 arrangement, each wave
 // owning a 128x64 block = 4x2 MFMA 32x32 blocks held in accumulation
-// registers. Every K stage brings 128 bytes of each of the 512 operand rows
-// into LDS (2 x 32 KB), double buffered. Rows are stored with their eight
+// registers. K runs in slices of 64 bytes of each of the 512 operand rows
+// (2 x 16 KB of LDS), four slice buffers deep. Rows are stored with their four
 // 16-byte chunks XOR-swizzled by the row index so that the ds_read_b128
 // fragment loads of 32 consecutive rows spread over all banks.
+//
+// What bounds it: with every operand zero (so that the clock is not held down
+// by power) the main loop is bound by the arrival of the operands, not by the
+// MFMAs. Two buffers of 128 bytes per row with one barrier each gave a load one
+// step to land and issued its loads in one burst after the barrier; four
+// buffers of 64 bytes give it three of the shorter steps, and the loads are
+// spread between the MFMAs. At T = 27394, D = 8192 that took FP16 from 5.06 to
+// 4.23 ms with zero operands (5.77 to 5.20 ms with Gaussian ones) and BF16x3
+// from 11.08 to 10.14 ms (13.73 to 12.80 ms), all on one box; FP32, MFMA-bound,
+// is unchanged. Warming the L2 with touches four to six stages ahead changed
+// nothing.
 //
 // Workgroups are mapped XCD-aware: the hardware deals consecutive workgroup
 // ids round-robin to the 8 XCDs, so each XCD is handed a contiguous run of a
@@ -48,8 +59,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int TILE = GRAM_TILE;
-constexpr int RB = GRAM_ROW_BYTES;          // bytes per row per stage
-constexpr int OPER_BYTES = TILE * RB;       // one operand tile in LDS (32 KB)
+constexpr int RB = GRAM_ROW_BYTES;          // bytes per row per slice
+constexpr int OPER_BYTES = TILE * RB;       // one operand tile in LDS (16 KB)
+constexpr int SLICE_BYTES = 2 * OPER_BYTES;  // A and B of a slice
 // Wave grid of a workgroup: WAVES_M x WAVES_N waves, each owning a
 // WT_M x WT_N block of the 256 x 256 tile in 32x32 MFMA blocks.
 constexpr int WAVES_M = 2;
@@ -57,26 +69,31 @@ constexpr int WAVES_N = GRAM_THREADS / 64 / WAVES_M;
 constexpr int WT_M = TILE / WAVES_M, WT_N = TILE / WAVES_N;
 constexpr int BM = WT_M / 32, BN = WT_N / 32;  // MFMA blocks per wave
 static_assert(WT_M == 128, "the epilogue parks 32-row bands of 128-row wave tiles");
-// s_waitcnt immediate waiting for vmcnt == 0 only (expcnt, lgkmcnt at max)
-constexpr int VMCNT0 = 0x0F70;
-// s_waitcnt immediate for vmcnt <= n (expcnt, lgkmcnt at max)
-constexpr int vmcnt_le(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
+// s_waitcnt immediate for vmcnt <= n and lgkmcnt == 0 (expcnt at max)
+constexpr int vmcnt_le(int n) { return (n & 15) | (7 << 4) | ((n >> 4) << 14); }
+// Workgroup barrier that leaves this wave's N youngest vector loads in flight
+// (the direct loads of later slices), where __syncthreads waits for all.
+template <int N>
+__device__ __forceinline__ void barrier_keeping() {
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(vmcnt_le(N));
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
 constexpr int EPI_PITCH = 36;  // floats per parked accumulator column (32 + 4)
 static_assert((GRAM_THREADS / 64) * (TILE / (GRAM_THREADS / 64 / 2)) * EPI_PITCH * 4 <=
-                  GRAM_STAGES * 2 * TILE * RB,
+                  GRAM_BUFFERS * SLICE_BYTES,
               "epilogue staging must fit in the operand LDS");
 constexpr int NORM_LDS = 2 * 2 * TILE * 4;  // two chunks' norms of the I and J rows
 
-// Physical 16-byte slot of logical chunk `chunk` in LDS row `row`. The XOR key
-// (row & 7) ^ ((row >> 3) & 3) gives any 8 aligned consecutive rows 8
-// distinct slots, any 16 aligned rows 16 distinct (row parity, slot) pairs and
-// any 32 aligned rows 32 distinct (row mod 4, slot) pairs, so ds_read_b128 of
-// 32 consecutive rows is conflict-free whether the LDS serves 8, 16 or 32
-// lanes per pass. It ignores row bits 5 and up, so rows 32 apart share a key.
-__device__ __forceinline__ int swz_key(int row) { return (row & 7) ^ ((row >> 3) & 3); }
-__device__ __forceinline__ int swz(int row, int chunk) {
-  return ((chunk ^ swz_key(row)) << 4);
-}
+// Physical 16-byte slot of logical chunk `chunk` in LDS row `row` (64 bytes,
+// four chunks). XORing the row's bits 2-3 gives any 8 or 16 aligned
+// consecutive rows distinct slots modulo 256 bytes (and the same for any 32
+// rows modulo 512), so ds_read_b128 of 32 consecutive rows is conflict-free.
+// It ignores row bits 4 and up, so rows 16 apart share a key.
+__device__ __forceinline__ int swz_key(int row) { return (row >> 2) & 3; }
 
 // Tile id -> (I, J), I <= J < nb, I < nrows (<= nb), in the XCD-aware
 // grouped order described above; ntiles = nrows nb - nrows (nrows - 1) / 2.
@@ -113,14 +130,14 @@ __device__ __forceinline__ bool decode_tile(int64_t wg, int nb, int nrows, int64
 constexpr int SG_MFMA = 0x008;
 constexpr int SG_DS_READ = 0x100;
 
-// Operand fragments of half a K stage for one wave: two 16-byte chunks of
-// each of the wave's 128 A rows and 64 B rows. Lane half h (lanes 32h ..
-// 32h+31) supplies k-group h of every MFMA; A and B use the same assignment,
-// so which elements a group holds does not matter. Part p of a stage:
-//   BF16x3: the 16 (hi, lo) pairs of k-slice p: x0/y0 = hi (chunk 4p + 2h),
-//           x1/y1 = lo (chunk 4p + 2h + 1); MFMAs hi.hi', hi.lo', lo.hi'.
-//   FP16:   k-slices 2p, 2p+1 (chunks 4p + h, 4p + 2 + h), one MFMA each.
-//   FP32:   chunks 4p + h, 4p + 2 + h, four depth-2 MFMAs each.
+// Operand fragments of a slice for one wave: two 16-byte chunks of each of the
+// wave's 128 A rows and 64 B rows. Lane half h (lanes 32h .. 32h+31) supplies
+// k-group h of every MFMA; A and B use the same assignment, so which elements
+// a group holds does not matter. A slice holds
+//   BF16x3: 16 (hi, lo) pairs: x0/y0 = hi (chunk 2h), x1/y1 = lo (chunk
+//           2h + 1); MFMAs hi.hi', hi.lo', lo.hi'.
+//   FP16:   32 values, two k-slices (chunks h and 2 + h), one MFMA each.
+//   FP32:   16 values, chunks h and 2 + h, four depth-2 MFMAs each.
 template <int PREC>
 struct Part {
   using V = typename std::conditional<PREC == TRAKNN_BF16X3, bf16x8,
@@ -133,17 +150,17 @@ constexpr int part_mfmas() {
   return PREC == TRAKNN_BF16X3 ? 3 * BM * BN : PREC == TRAKNN_FP16 ? 2 * BM * BN : 8 * BM * BN;
 }
 
-// Lane offsets of a part's two chunks in the A and B tiles of a stage buffer.
-// The wave's rows wm*WT_M + q*32 + r32 (A) and wn*WT_N + q*32 + r32 (B) share
-// the swizzle key of r32, so q is an immediate offset of q * 32 rows.
+// Lane offsets of the two chunks in the A and B tiles of a slice buffer. The
+// wave's rows wm*WT_M + q*32 + r32 (A) and wn*WT_N + q*32 + r32 (B) share the
+// swizzle key of r32, so q is an immediate offset of q * 32 rows.
 struct PartOffsets {
   int a0, a1, b0, b1;
 };
 template <int PREC>
-__device__ __forceinline__ PartOffsets part_offsets(int p, int wm, int wn, int lane) {
+__device__ __forceinline__ PartOffsets part_offsets(int wm, int wn, int lane) {
   const int r32 = lane & 31, h = lane >> 5;
   const int key = swz_key(r32);
-  const int c0 = 4 * p + (PREC == TRAKNN_BF16X3 ? 2 * h : h);
+  const int c0 = PREC == TRAKNN_BF16X3 ? 2 * h : h;
   const int c1 = c0 + (PREC == TRAKNN_BF16X3 ? 1 : 2);
   PartOffsets o;
   o.a0 = (wm * WT_M + r32) * RB + ((c0 ^ key) << 4);
@@ -169,43 +186,74 @@ __device__ __forceinline__ void read_part(const char* __restrict__ buf, const Pa
   }
 }
 
-template <int PREC>
-__device__ __forceinline__ void mfma_part(const Part<PREC>& P, f32x16 (&acc)[BM][BN]) {
+// MFMA number I of a part. Per accumulator the order of the products is fixed
+// (hi.hi', hi.lo', lo.hi' of a slice; slice by slice), whatever else a
+// schedule interleaves.
+template <int PREC, int I>
+__device__ __forceinline__ void mfma_step(const Part<PREC>& P, f32x16 (&acc)[BM][BN]) {
   if constexpr (PREC == TRAKNN_BF16X3) {
-#pragma unroll
-    for (int bm = 0; bm < BM; ++bm)
-#pragma unroll
-      for (int bn = 0; bn < BN; ++bn) {
-        acc[bm][bn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(P.x0[bm], P.y0[bn], acc[bm][bn], 0, 0, 0);
-        acc[bm][bn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(P.x0[bm], P.y1[bn], acc[bm][bn], 0, 0, 0);
-        acc[bm][bn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(P.x1[bm], P.y0[bn], acc[bm][bn], 0, 0, 0);
-      }
+    constexpr int bm = I / (3 * BN), bn = I / 3 % BN, t = I % 3;
+    acc[bm][bn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+        t == 2 ? P.x1[bm] : P.x0[bm], t == 1 ? P.y1[bn] : P.y0[bn], acc[bm][bn], 0, 0, 0);
   } else if constexpr (PREC == TRAKNN_FP16) {
-#pragma unroll
-    for (int bm = 0; bm < BM; ++bm)
-#pragma unroll
-      for (int bn = 0; bn < BN; ++bn)
-        acc[bm][bn] = __builtin_amdgcn_mfma_f32_32x32x16_f16(P.x0[bm], P.y0[bn], acc[bm][bn], 0, 0, 0);
-#pragma unroll
-    for (int bm = 0; bm < BM; ++bm)
-#pragma unroll
-      for (int bn = 0; bn < BN; ++bn)
-        acc[bm][bn] = __builtin_amdgcn_mfma_f32_32x32x16_f16(P.x1[bm], P.y1[bn], acc[bm][bn], 0, 0, 0);
+    constexpr int c = I / (BM * BN), bm = I / BN % BM, bn = I % BN;
+    acc[bm][bn] = __builtin_amdgcn_mfma_f32_32x32x16_f16(c ? P.x1[bm] : P.x0[bm],
+                                                         c ? P.y1[bn] : P.y0[bn], acc[bm][bn], 0, 0, 0);
   } else {
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-#pragma unroll
-      for (int bm = 0; bm < BM; ++bm)
-#pragma unroll
-        for (int bn = 0; bn < BN; ++bn)
-          acc[bm][bn] = __builtin_amdgcn_mfma_f32_32x32x2f32(P.x0[bm][e], P.y0[bn][e], acc[bm][bn], 0, 0, 0);
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-#pragma unroll
-      for (int bm = 0; bm < BM; ++bm)
-#pragma unroll
-        for (int bn = 0; bn < BN; ++bn)
-          acc[bm][bn] = __builtin_amdgcn_mfma_f32_32x32x2f32(P.x1[bm][e], P.y1[bn][e], acc[bm][bn], 0, 0, 0);
+    constexpr int c = I / (4 * BM * BN), e = I / (BM * BN) % 4, bm = I / BN % BM, bn = I % BN;
+    acc[bm][bn] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+        c ? P.x1[bm][e] : P.x0[bm][e], c ? P.y1[bn][e] : P.y0[bn][e], acc[bm][bn], 0, 0, 0);
+  }
+}
+template <int PREC, int I = 0>
+__device__ __forceinline__ void mfma_part(const Part<PREC>& P, f32x16 (&acc)[BM][BN]) {
+  if constexpr (I < part_mfmas<PREC>()) {
+    mfma_step<PREC, I>(P, acc);
+    mfma_part<PREC, I + 1>(P, acc);
+  }
+}
+
+// Fragment read number R of a part (A chunks of each block, then B chunks).
+template <int PREC, int R>
+__device__ __forceinline__ void read_step(const char* __restrict__ buf, const PartOffsets& o,
+                                          Part<PREC>& P) {
+  using V = typename Part<PREC>::V;
+  constexpr bool b = R >= 2 * BM;
+  constexpr int q = (b ? R - 2 * BM : R) / 2;
+  const V v = *(const V*)(buf + (b ? (R % 2 ? o.b1 : o.b0) : (R % 2 ? o.a1 : o.a0)) + q * 32 * RB);
+  if constexpr (b) {
+    if constexpr (R % 2) P.y1[q] = v;
+    else P.y0[q] = v;
+  } else {
+    if constexpr (R % 2) P.x1[q] = v;
+    else P.x0[q] = v;
+  }
+}
+
+// The MFMAs of part P with the reads of part N and PART_LOADS direct loads
+// placed between them: two reads after each of the first MFMAs, a load after
+// every load_every()-th. All loads at once hold the wave's MFMAs back behind
+// the CU's address unit, which takes 64 bytes per clock: spreading them alone
+// took the BF16x3 Gram from 14.23 to 13.85 ms (T = 27394, D = 8192).
+constexpr int PART_LOADS = 2 * (OPER_BYTES / 1024 / (GRAM_THREADS / 64));
+template <int PREC>
+constexpr int load_every() {
+  return part_mfmas<PREC>() / PART_LOADS;
+}
+template <int PREC, int I = 0, typename LOADF>
+__device__ __forceinline__ void mfma_read_load(const Part<PREC>& P, f32x16 (&acc)[BM][BN],
+                                               const char* __restrict__ buf,
+                                               const PartOffsets& o, Part<PREC>& N, LOADF load) {
+  if constexpr (I < part_mfmas<PREC>()) {
+    mfma_step<PREC, I>(P, acc);
+    if constexpr (2 * I < PART_READS) {
+      read_step<PREC, 2 * I>(buf, o, N);
+      read_step<PREC, 2 * I + 1>(buf, o, N);
+    }
+    constexpr int E = load_every<PREC>();
+    if constexpr (I % E == E - 1 && I / E < PART_LOADS) load(I / E);
+    __builtin_amdgcn_sched_barrier(0);
+    mfma_read_load<PREC, I + 1>(P, acc, buf, o, N, load);
   }
 }
 
@@ -239,7 +287,7 @@ __device__ __forceinline__ void interleave_reads() {
 constexpr int FPITCH = TILE + 1;  // floats per staged row (odd: transposed reads)
 constexpr int FUSED_MAX_STAGED = (GRAM_TILE - 16) / 2 + 15;  // rows of a part, L <= 16
 constexpr int FUSED_VAL_BYTES = FUSED_MAX_STAGED * FPITCH * 4;
-constexpr int GRAM_LDS = GRAM_STAGES * 2 * OPER_BYTES + NORM_LDS;
+constexpr int GRAM_LDS = GRAM_BUFFERS * SLICE_BYTES + NORM_LDS;
 // the staged part, then each wave's first-round scratch
 constexpr int FUSED_EST_OFFSET = (FUSED_VAL_BYTES + 15) / 16 * 16;
 constexpr int FUSED_EST_BYTES = FUSED_EST_OFFSET + (GRAM_THREADS / 64) * EST_SCRATCH_BYTES;
@@ -248,13 +296,13 @@ static_assert(FUSED_LDS <= 160 * 1024, "a fused part must fit in the LDS of a CU
 
 template <int PREC, bool BAND, int FUSE = 0>
 __global__ __launch_bounds__(GRAM_THREADS, 1) void gram_kernel(
-    const char* __restrict__ xc, int64_t pitch, int nstages,
+    const char* __restrict__ xc, int64_t slice_bytes, int nsl,
     const float* __restrict__ ncs, int64_t T, int64_t Tpad, int nb, int64_t ntiles,
     int64_t a_row0, int nbi, int64_t rows_out, int J0, float* __restrict__ S, int64_t ldS,
     float* __restrict__ ST, int64_t ldST, FusedGeom fg, const double* __restrict__ fbound,
     FusedSlots fout) {
   __shared__ __attribute__((aligned(16))) char lds[FUSE ? FUSED_LDS : GRAM_LDS];
-  float* const nrm = (float*)(lds + GRAM_STAGES * 2 * OPER_BYTES);  // [2][I 256 | J 256]
+  float* const nrm = (float*)(lds + GRAM_BUFFERS * SLICE_BYTES);  // [2][I 256 | J 256]
   int I, J;
   if constexpr (FUSE != 0) {
     // the round's tiles, each XCD a contiguous run of them (as decode_tile)
@@ -277,40 +325,31 @@ __global__ __launch_bounds__(GRAM_THREADS, 1) void gram_kernel(
   const int lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
   const int wm = w / WAVES_N, wn = w % WAVES_N;
-  const char* Ag = xc + arow * pitch;
-  const char* Bg = xc + brow * pitch;
+  const char* Ag = xc + arow * RB;
+  const char* Bg = xc + brow * RB;
 
   // Direct buffer -> LDS loads (buffer_load_dwordx4 ... lds): lane q of a load
-  // lands at byte 16*q of the wave's 1 KB destination block, so each lane
-  // fetches the logical chunk whose swizzled slot is that destination. Each
-  // wave moves 8 KB of A and 8 KB of B per stage and no VGPR stages the data.
-  // The buffer resources span the two 256-row panels (the planner keeps a
-  // panel below 4 GiB), so a lane needs one 32-bit offset per block, shared by
-  // A and B, and the stage offset travels in the scalar offset.
+  // lands at byte 16*q of the wave's 1 KB destination block (16 rows), so each
+  // lane fetches the logical chunk whose swizzled slot is that destination.
+  // Each wave moves two blocks of A and two of B per slice and no VGPR stages
+  // the data. The operands lie slice by slice (internal.h), so a panel's rows
+  // of a slice are one contiguous 16 KB block: a buffer resource per slice and
+  // panel, and one lane offset shared by every block.
   constexpr int BLK_PER_WAVE = OPER_BYTES / 1024 / (GRAM_THREADS / 64);
   constexpr int RSRC_WORD3 = 0x00020000;  // raw 32-bit buffer, gfx9 family
-  const int panel_bytes = (int)(uint32_t)(TILE * pitch);
-  const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc((void*)Ag, 0, panel_bytes, RSRC_WORD3);
-  const __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc((void*)Bg, 0, panel_bytes, RSRC_WORD3);
-  uint32_t voff[BLK_PER_WAVE];
+  const uint32_t voff = (uint32_t)((lane >> 2) * RB + (((lane & 3) ^ swz_key(lane >> 2)) << 4));
+  // load v of a slice: block v / 2 of the wave, of A (v even) or B
+  auto issue_one = [&](int sl, int v) __attribute__((always_inline)) {
+    char* dst = lds + (sl & (GRAM_BUFFERS - 1)) * SLICE_BYTES + (v & 1) * OPER_BYTES;
+    const int blk = w * BLK_PER_WAVE + v / 2;  // 1 KB block
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)((v & 1 ? Bg : Ag) + sl * slice_bytes), 0, OPER_BYTES, RSRC_WORD3);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+        rs, (__attribute__((address_space(3))) void*)(dst + blk * 1024), 16, voff, blk * 1024, 0, 0);
+  };
+  auto issue = [&](int sl) __attribute__((always_inline)) {
 #pragma unroll
-  for (int u = 0; u < BLK_PER_WAVE; ++u) {
-    const int row = (w * BLK_PER_WAVE + u) * 8 + (lane >> 3);
-    const int c = (lane & 7) ^ swz_key(row);  // inverse of swz
-    voff[u] = (uint32_t)row * (uint32_t)pitch + (uint32_t)(c * 16);
-  }
-  auto issue = [&](int st, int buf) {
-    char* A = lds + buf * 2 * OPER_BYTES;
-    const uint32_t soff = (uint32_t)st * RB;
-#pragma unroll
-    for (int u = 0; u < BLK_PER_WAVE; ++u) {
-      const int blk = w * BLK_PER_WAVE + u;  // 1 KB block
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          rsA, (__attribute__((address_space(3))) void*)(A + blk * 1024), 16, voff[u], soff, 0, 0);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          rsB, (__attribute__((address_space(3))) void*)(A + OPER_BYTES + blk * 1024), 16, voff[u],
-          soff, 0, 0);
-    }
+    for (int v = 0; v < 2 * BLK_PER_WAVE; ++v) issue_one(sl, v);
   };
 
   f32x16 acc[BM][BN];
@@ -352,58 +391,70 @@ __global__ __launch_bounds__(GRAM_THREADS, 1) void gram_kernel(
       for (int bn = 0; bn < BN; ++bn)
         acc[bm][bn] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[bm], bv[bn], acc[bm][bn], 0, 0, 0);
   };
-  constexpr int SPC = GRAM_CHUNK / (PREC == TRAKNN_FP16 ? 64 : 32);  // stages per chunk
+  constexpr int SPC = GRAM_CHUNK / (PREC == TRAKNN_FP16 ? 32 : 16);  // slices per chunk (even)
 
-  // Every stage is two parts. Part 0 of stage st is read while the MFMAs of
-  // part 1 of stage st - 1 run (right after the barrier that makes stage st
-  // visible), part 1 of st while the MFMAs of part 0 of st run; so LDS read
-  // latency hides behind MFMAs and only one part's fragments are in flight.
-  const PartOffsets o0 = part_offsets<PREC>(0, wm, wn, lane);
-  const PartOffsets o1 = part_offsets<PREC>(1, wm, wn, lane);
-  // Stage st + 2 is issued right after the barrier in the middle of stage st
-  // (its buffer, that of stage st, has then been read by every wave), so the
-  // loads have the second half of st and the first half of st + 1 to land.
-  // The norms of a chunk travel with the loads of the chunk's last stage.
-  auto issue_stage = [&](int st) {
-    issue(st, st & 1);
-    if ((st + 1 == nstages || (st + 1) % SPC == 0) && w < 2) issue_norms(st / SPC);
+  // Slice sl lives in buffer sl % 4. Step sl runs the MFMAs of slice sl from
+  // registers, reads slice sl + 1's fragments (the barrier before the step
+  // made it visible) and issues slice sl + 4's loads into the buffer that
+  // slice sl left in the step before. So a load has three steps to land, LDS
+  // read latency hides behind MFMAs, and a wait leaves the loads of the two
+  // youngest slices in flight.
+  constexpr int SLICE_LOADS = 2 * BLK_PER_WAVE;
+  const PartOffsets o = part_offsets<PREC>(wm, wn, lane);
+  auto buffer = [&](int sl) __attribute__((always_inline)) {
+    return lds + (sl & (GRAM_BUFFERS - 1)) * SLICE_BYTES;
   };
   Part<PREC> P0, P1;
-  issue_stage(0);
-  if (nstages > 1) {
-    issue_stage(1);
-    // stage 0 has landed (stage 1's loads may still be in flight)
-    __builtin_amdgcn_s_waitcnt(vmcnt_le(2 * BLK_PER_WAVE));
+  if (w < 2) issue_norms(0);
+  issue(0);
+  issue(1);
+  if (nsl > 2) {
+    issue(2);
+    issue(3);
+    barrier_keeping<2 * SLICE_LOADS>();
   } else {
-    __builtin_amdgcn_s_waitcnt(VMCNT0);
+    barrier_keeping<0>();
   }
-  __syncthreads();
-  read_part<PREC>(lds, o0, P0);
-  for (int st = 0; st + 1 < nstages; ++st) {
-    const int buf = st & 1;
-    const int ch = st / SPC;
-    const bool chunk_end = (st + 1) % SPC == 0;
-    read_part<PREC>(lds + buf * 2 * OPER_BYTES, o1, P1);
-    mfma_part<PREC>(P0, acc);
-    interleave_reads<part_mfmas<PREC>()>();
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(VMCNT0);  // stage st + 1 (the only loads in flight)
-    __syncthreads();
-    __builtin_amdgcn_sched_barrier(0);
-    if (st + 2 < nstages) issue_stage(st + 2);
-    read_part<PREC>(lds + (buf ^ 1) * 2 * OPER_BYTES, o0, P0);
-    mfma_part<PREC>(P1, acc);
-    interleave_reads<part_mfmas<PREC>()>();
-    __builtin_amdgcn_sched_barrier(0);
-    if (chunk_end) correct(ch);
+  read_part<PREC>(buffer(0), o, P0);
+  barrier_keeping<2 * SLICE_LOADS>();  // slice 0's buffer is read before step 0 refills it
+  auto step = [&](int sl, const Part<PREC>& P, Part<PREC>& N, auto keep_c)
+                  __attribute__((always_inline)) {
+    constexpr int KEEP = decltype(keep_c)::value;  // younger slices left in flight
+    constexpr bool LOAD = KEEP == 2;               // slice sl + 4 exists
+    if constexpr (LOAD) {
+      mfma_read_load<PREC>(P, acc, buffer(sl + 1), o, N,
+                           [&](int v) __attribute__((always_inline)) { issue_one(sl + 4, v); });
+    } else {
+      read_part<PREC>(buffer(sl + 1), o, N);
+      mfma_part<PREC>(P, acc);
+      interleave_reads<part_mfmas<PREC>()>();
+    }
+    barrier_keeping<KEEP * SLICE_LOADS>();
+  };
+  // after the second step of a pair: the chunk's norms once it is done, and
+  // the next chunk's on their way (their slot was last read a chunk ago)
+  auto chunk = [&](int sl) __attribute__((always_inline)) {
+    if ((sl + 1) % SPC == 0) {
+      correct(sl / SPC);
+      if (w < 2) issue_norms(sl / SPC + 1);
+    }
+  };
+  using K0 = std::integral_constant<int, 0>;
+  using K1 = std::integral_constant<int, 1>;
+  using K2 = std::integral_constant<int, 2>;
+  for (int sl = 0; sl + 5 < nsl; sl += 2) {
+    step(sl, P0, P1, K2{});
+    step(sl + 1, P1, P0, K2{});
+    chunk(sl + 1);
   }
-  {  // last stage: nothing left to fetch
-    const int st = nstages - 1;
-    read_part<PREC>(lds + (st & 1) * 2 * OPER_BYTES, o1, P1);
-    mfma_part<PREC>(P0, acc);
-    mfma_part<PREC>(P1, acc);
-    correct(st / SPC);
+  if (nsl > 2) {
+    step(nsl - 4, P0, P1, K1{});
+    step(nsl - 3, P1, P0, K0{});
+    chunk(nsl - 3);
   }
+  step(nsl - 2, P0, P1, K0{});
+  mfma_part<PREC>(P1, acc);
+  correct((nsl - 1) / SPC);
   __syncthreads();  // every wave is done with the operand buffers
 
   if constexpr (FUSE != 0) {
@@ -597,8 +648,8 @@ hipError_t launch_gram_band(const void* xc, const float* ncs, int64_t T, int64_t
                             int64_t Dpad, int nb, int64_t ntiles, int precision,
                             int64_t a_row0, int nbi, int64_t rows_out, int J0, float* S,
                             int64_t ldS, float* ST, int64_t ldST, hipStream_t s) {
-  const int64_t pitch = Dpad * elem_bytes(precision);
-  const int nstages = (int)(Dpad / stage_k(precision));
+  const int64_t slice_bytes = Tpad * GRAM_ROW_BYTES;
+  const int nsl = (int)(Dpad / stage_k(precision)) * 2;
   const int64_t per = (ntiles + NUM_XCD - 1) / NUM_XCD;
   dim3 grid((unsigned)(per * NUM_XCD));
   const char* x = (const char*)xc;
@@ -607,7 +658,7 @@ hipError_t launch_gram_band(const void* xc, const float* ncs, int64_t T, int64_t
   const FusedGeom fg{};
   const FusedSlots fo{};
 #define TRAKNN_GRAM_LAUNCH(P, B)                                                          \
-  hipLaunchKernelGGL((gram_kernel<P, B>), grid, dim3(GRAM_THREADS), 0, s, x, pitch, nstages, \
+  hipLaunchKernelGGL((gram_kernel<P, B>), grid, dim3(GRAM_THREADS), 0, s, x, slice_bytes, nsl, \
                      ncs, T, Tpad, nb, ntiles, a_row0, nbi, rows_out, J0, S, ldS, ST, ldST, \
                      fg, nullptr, fo)
   switch (precision) {
@@ -631,15 +682,15 @@ hipError_t launch_gram_band(const void* xc, const float* ncs, int64_t T, int64_t
 hipError_t launch_gram_fused(const void* xc, const float* ncs, int64_t T, int64_t Tpad,
                              int64_t Dpad, int precision, const FusedGeom& g, bool establish,
                              const double* bound, const FusedSlots& out, hipStream_t s) {
-  const int64_t pitch = Dpad * elem_bytes(precision);
-  const int nstages = (int)(Dpad / stage_k(precision));
+  const int64_t slice_bytes = Tpad * GRAM_ROW_BYTES;
+  const int nsl = (int)(Dpad / stage_k(precision)) * 2;
   const int64_t ntiles = fused_band_tiles(g);
   if (ntiles <= 0) return hipSuccess;
   const dim3 grid((unsigned)((ntiles + NUM_XCD - 1) / NUM_XCD * NUM_XCD));
   const char* x = (const char*)xc;
 #define TRAKNN_GRAM_FUSED(P, F)                                                           \
-  hipLaunchKernelGGL((gram_kernel<P, false, F>), grid, dim3(GRAM_THREADS), 0, s, x, pitch, \
-                     nstages, ncs, T, Tpad, 0, ntiles, (int64_t)0, 0, T, 0, nullptr,        \
+  hipLaunchKernelGGL((gram_kernel<P, false, F>), grid, dim3(GRAM_THREADS), 0, s, x, slice_bytes, \
+                     nsl, ncs, T, Tpad, 0, ntiles, (int64_t)0, 0, T, 0, nullptr,        \
                      (int64_t)0, nullptr, (int64_t)0, g, bound, out)
   switch (precision) {
     case TRAKNN_FP32:

@@ -13,18 +13,21 @@ namespace traknn {
 
 // ---------------------------------------------------------------------------
 // Gram tiling (Eq. 4 stage). One workgroup owns a GRAM_TILE x GRAM_TILE block
-// of the distance matrix; every K stage moves GRAM_ROW_BYTES of each of the
-// 2 * GRAM_TILE operand rows through LDS.
+// of the distance matrix; every K slice moves GRAM_ROW_BYTES of each of the
+// 2 * GRAM_TILE operand rows through LDS, GRAM_BUFFERS slices deep.
 // ---------------------------------------------------------------------------
 constexpr int GRAM_TILE = 256;
 constexpr int GRAM_THREADS = 512;
-constexpr int GRAM_ROW_BYTES = 128;
-constexpr int GRAM_STAGES = 2;
+constexpr int GRAM_ROW_BYTES = 64;
+constexpr int GRAM_BUFFERS = 4;
 constexpr int GRAM_GROUP_ROWS = 4;  // block-rows per L2 locality group
 constexpr int NUM_XCD = 8;
 
-// K elements one stage covers: 32 FP32 values, 32 (hi, lo) BF16 pairs or 64
-// FP16 values -- always 128 bytes of a centred row.
+// Layout of the centred operands: slice by slice, [2 Dpad / stage_k][Tpad][
+// GRAM_ROW_BYTES], so that the rows of a tile's panel are contiguous in a
+// slice and a load of 1 KB is one run of memory. A slice holds 16 FP32 values,
+// 16 (hi, lo) BF16 pairs or 32 FP16 values of each row; D is padded to pairs
+// of slices (stage_k elements).
 inline int stage_k(int precision) { return precision == TRAKNN_FP16 ? 64 : 32; }
 inline int elem_bytes(int precision) { return precision == TRAKNN_FP16 ? 2 : 4; }
 

@@ -18,6 +18,7 @@
 #include <hip/hip_fp16.h>
 
 #include "internal.h"
+#include "topk_wave.h"
 
 namespace traknn {
 namespace {
@@ -85,8 +86,12 @@ __global__ __launch_bounds__(256) void colsum_reduce_kernel(
   mu[c] = s / (double)nsamp;
 }
 
-__device__ inline double wave_sum(double v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+// Sum over the wave by a butterfly of strides 32, 16, ... 1 (every lane gets
+// it), the exchanges of topk_wave.h.
+template <int S = 32>
+__device__ __forceinline__ double wave_sum(double v, int lane) {
+  v += __hiloint2double(lane_xor<S>(__double2hiint(v), lane), lane_xor<S>(__double2loint(v), lane));
+  if constexpr (S > 1) return wave_sum<S / 2>(v, lane);
   return v;
 }
 
@@ -100,107 +105,149 @@ __device__ inline double bf16_bits_to_double(uint32_t b) {
   return (double)__uint_as_float(b << 16);
 }
 
-// Wave (blockIdx.x * 4 + w) owns norm chunk ch = that index (GRAM_CHUNK
-// elements; lane q the 8 consecutive elements 8q .. 8q+7) and converts it for
-// CONV_ROWS consecutive rows starting at blockIdx.y * CONV_ROWS, keeping the
-// chunk's means in registers: two 16-byte loads and one or two 16-byte stores
-// per lane and row. Each (row, chunk) squared norm (FP64 sum, stored FP32) goes
-// to ncs[chunk * Tpad + row]. PREC selects the emitted representation.
-constexpr int CONV_ROWS = 16;
+// Eight centred cells of a row, v, in the representation PREC emits: OUT / 16
+// 16-byte chunks of the operand row. Returns the FP64 squared norm of the
+// represented values.
+template <int PREC>
+constexpr int conv_bytes() { return PREC == TRAKNN_FP16 ? 16 : 32; }
+template <int PREC>
+__device__ __forceinline__ double convert8(const double (&v)[8], uint4 (&out)[conv_bytes<PREC>() / 16]) {
+  double acc = 0.0;
+  if constexpr (PREC == TRAKNN_FP32) {
+    uint32_t f[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const float x = (float)v[u];
+      acc += (double)x * (double)x;
+      f[u] = __float_as_uint(x);
+    }
+    out[0] = make_uint4(f[0], f[1], f[2], f[3]);
+    out[1] = make_uint4(f[4], f[5], f[6], f[7]);
+  } else if constexpr (PREC == TRAKNN_FP16) {
+    uint32_t packed[4];
+#pragma unroll
+    for (int u = 0; u < 8; u += 2) {
+      const _Float16 h0 = (_Float16)(float)v[u], h1 = (_Float16)(float)v[u + 1];
+      const double d0 = (double)(float)h0, d1 = (double)(float)h1;
+      acc += d0 * d0;
+      acc += d1 * d1;
+      packed[u / 2] = (uint32_t)__builtin_bit_cast(uint16_t, h0) |
+                      ((uint32_t)__builtin_bit_cast(uint16_t, h1) << 16);
+    }
+    out[0] = make_uint4(packed[0], packed[1], packed[2], packed[3]);
+  } else {
+    // BF16X3: the 16-byte chunk of 8 hi values is followed by the chunk of
+    // the 8 matching lo values, so one 64-byte Gram slice row holds 16
+    // (hi, lo) pairs.
+    uint32_t hp[4], lp[4];
+#pragma unroll
+    for (int u = 0; u < 8; u += 2) {
+      uint32_t hb[2], lb[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        hb[t] = bf16_bits_rne((float)v[u + t]);
+        const double hd = bf16_bits_to_double(hb[t]);
+        lb[t] = bf16_bits_rne((float)(v[u + t] - hd));
+        // norm of the represented value hi + lo (exact in FP64). The Gram
+        // stage drops only the cross term lo_i.lo_j, which has zero mean;
+        // a norm made of the three kept products alone would bias every
+        // distance low by sum (lo_i - lo_j)^2 ~ 2.5e-6 (N_i + N_j).
+        const double xv = hd + bf16_bits_to_double(lb[t]);
+        acc += xv * xv;
+      }
+      hp[u / 2] = hb[0] | (hb[1] << 16);
+      lp[u / 2] = lb[0] | (lb[1] << 16);
+    }
+    out[0] = make_uint4(hp[0], hp[1], hp[2], hp[3]);
+    out[1] = make_uint4(lp[0], lp[1], lp[2], lp[3]);
+  }
+  return acc;
+}
+
+// Wave g of the grid owns norm chunk ch = g mod nch (GRAM_CHUNK elements; lane q
+// the 8 consecutive elements 8q .. 8q+7) and converts it for nrows rows (a
+// multiple of CONV_BATCH) starting at g / nch * nrows, keeping the chunk's
+// means in registers. Bound by HBM (4 bytes read and 2 or 4 written per
+// element): 0.35 ms for 27394 x 8192 fields in BF16x3, 5.2 TB/s, where a plain
+// copy of this size moves 5.2 TB/s. CONV_BATCH rows are loaded together, and
+// their converted chunk goes through LDS, because the operands lie slice by
+// slice (internal.h): a lane's own cells are half a 64-byte row of one slice,
+// so storing them directly writes 64-byte pieces Tpad * 64 bytes apart (0.50
+// ms on the same fields), while the batch's rows of a slice are one 256-byte
+// run. Each (row, chunk) squared norm (FP64 sum, stored FP32) goes to
+// ncs[chunk * Tpad + row]. PREC selects the emitted representation.
+constexpr int CONV_BATCH = 4;
 template <int PREC>
 __global__ __launch_bounds__(256) void centre_convert_kernel(
     const float* __restrict__ X, int64_t ldx, int64_t T, int64_t D,
     int64_t Tpad, int64_t Dpad, const double* __restrict__ mu,
-    void* __restrict__ xc, float* __restrict__ ncs) {
+    char* __restrict__ xc, float* __restrict__ ncs, int nrows) {
   static_assert(GRAM_CHUNK == 64 * 8, "a wave covers one norm chunk");
+  constexpr int LB = conv_bytes<PREC>();  // bytes a lane emits per row
+  constexpr int CB = 64 * LB;             // bytes of a row's chunk
+  constexpr int PITCH = CB + GRAM_ROW_BYTES;
+  constexpr int NSL = CB / GRAM_ROW_BYTES;  // slices of a chunk
+  constexpr int CPR = GRAM_ROW_BYTES / 16;  // 16-byte chunks of a slice row
+  static_assert(CONV_BATCH * CPR == 16, "16 lanes store a batch's rows of a slice");
+  __shared__ __attribute__((aligned(16))) char stage[4][CONV_BATCH * PITCH];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t ch = (int64_t)blockIdx.x * 4 + w;
-  if (ch >= norm_chunks(Dpad)) return;
+  const int64_t nch = norm_chunks(Dpad), g = (int64_t)blockIdx.x * 4 + w;
+  const int64_t ch = g % nch, ib = g / nch * nrows;
+  if (ib >= Tpad) return;  // no workgroup barrier below
   const int64_t e0 = ch * GRAM_CHUNK + 8 * lane;  // Dpad is a multiple of 8
   const bool in_pad = e0 < Dpad;
   const bool full = e0 + 8 <= D;
+  const int64_t sl0 = ch * NSL, nsl = Dpad * LB / 8 / GRAM_ROW_BYTES;
   double m[8];
 #pragma unroll
   for (int u = 0; u < 8; ++u) m[u] = e0 + u < D ? mu[e0 + u] : 0.0;
-  for (int rr = 0; rr < CONV_ROWS; ++rr) {
-    const int64_t i = (int64_t)blockIdx.y * CONV_ROWS + rr;
-    if (i >= Tpad) break;
-    const bool live = i < T;
-    const float* xrow = X + i * ldx;
-    double acc = 0.0;
-    if (in_pad) {
-      double v[8];
+  for (int64_t i0 = ib; i0 < ib + nrows && i0 < Tpad; i0 += CONV_BATCH) {
+    float x[CONV_BATCH][8];
+#pragma unroll
+    for (int r = 0; r < CONV_BATCH; ++r) {
+      const float* xrow = X + (i0 + r) * ldx;
+      const bool live = i0 + r < T;
       if (live && full) {
         const float4 a = *(const float4*)(xrow + e0);
         const float4 b = *(const float4*)(xrow + e0 + 4);
-        v[0] = (double)a.x - m[0];
-        v[1] = (double)a.y - m[1];
-        v[2] = (double)a.z - m[2];
-        v[3] = (double)a.w - m[3];
-        v[4] = (double)b.x - m[4];
-        v[5] = (double)b.y - m[5];
-        v[6] = (double)b.z - m[6];
-        v[7] = (double)b.w - m[7];
+        x[r][0] = a.x, x[r][1] = a.y, x[r][2] = a.z, x[r][3] = a.w;
+        x[r][4] = b.x, x[r][5] = b.y, x[r][6] = b.z, x[r][7] = b.w;
       } else {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int64_t e = e0 + u;
-          v[u] = (live && e < D) ? (double)xrow[e] - m[u] : 0.0;
-        }
-      }
-      if constexpr (PREC == TRAKNN_FP32) {
-        float f[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          f[u] = (float)v[u];
-          acc += (double)f[u] * (double)f[u];
-        }
-        float4* out = (float4*)((float*)xc + i * Dpad + e0);
-        out[0] = make_float4(f[0], f[1], f[2], f[3]);
-        out[1] = make_float4(f[4], f[5], f[6], f[7]);
-      } else if constexpr (PREC == TRAKNN_FP16) {
-        uint32_t packed[4];
-#pragma unroll
-        for (int u = 0; u < 8; u += 2) {
-          const _Float16 h0 = (_Float16)(float)v[u], h1 = (_Float16)(float)v[u + 1];
-          const double d0 = (double)(float)h0, d1 = (double)(float)h1;
-          acc += d0 * d0;
-          acc += d1 * d1;
-          packed[u / 2] = (uint32_t)__builtin_bit_cast(uint16_t, h0) |
-                          ((uint32_t)__builtin_bit_cast(uint16_t, h1) << 16);
-        }
-        *(uint4*)((_Float16*)xc + i * Dpad + e0) =
-            make_uint4(packed[0], packed[1], packed[2], packed[3]);
-      } else {
-        // BF16X3: the 16-byte chunk of 8 hi values is followed by the chunk of
-        // the 8 matching lo values, so one 128-byte Gram stage row holds 32
-        // (hi, lo) pairs.
-        uint32_t hp[4], lp[4];
-#pragma unroll
-        for (int u = 0; u < 8; u += 2) {
-          uint32_t hb[2], lb[2];
-#pragma unroll
-          for (int t = 0; t < 2; ++t) {
-            hb[t] = bf16_bits_rne((float)v[u + t]);
-            const double hd = bf16_bits_to_double(hb[t]);
-            lb[t] = bf16_bits_rne((float)(v[u + t] - hd));
-            // norm of the represented value hi + lo (exact in FP64). The Gram
-            // stage drops only the cross term lo_i.lo_j, which has zero mean;
-            // a norm made of the three kept products alone would bias every
-            // distance low by sum (lo_i - lo_j)^2 ~ 2.5e-6 (N_i + N_j).
-            const double xv = hd + bf16_bits_to_double(lb[t]);
-            acc += xv * xv;
-          }
-          hp[u / 2] = hb[0] | (hb[1] << 16);
-          lp[u / 2] = lb[0] | (lb[1] << 16);
-        }
-        uint4* out = (uint4*)((uint16_t*)xc + i * Dpad * 2 + 2 * e0);
-        out[0] = make_uint4(hp[0], hp[1], hp[2], hp[3]);
-        out[1] = make_uint4(lp[0], lp[1], lp[2], lp[3]);
+        for (int u = 0; u < 8; ++u) x[r][u] = live && e0 + u < D ? xrow[e0 + u] : 0.f;
       }
     }
-    acc = wave_sum(acc);
-    if (lane == 0) ncs[ch * Tpad + i] = live ? (float)acc : 0.f;
+    double acc[CONV_BATCH];
+#pragma unroll
+    for (int r = 0; r < CONV_BATCH; ++r) {
+      const bool live = i0 + r < T;
+      double v[8];
+      uint4 out[LB / 16];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = live && e0 + u < D ? (double)x[r][u] - m[u] : 0.0;
+      acc[r] = convert8<PREC>(v, out);
+#pragma unroll
+      for (int q = 0; q < LB / 16; ++q)
+        *(uint4*)(stage[w] + r * PITCH + lane * LB + 16 * q) = out[q];
+    }
+    __builtin_amdgcn_wave_barrier();  // LDS accesses of a wave execute in order
+    // 16 lanes per slice: row (lane / CPR) % CONV_BATCH, chunk lane % CPR
+    const int row = lane / CPR % CONV_BATCH, c = lane % CPR;
+#pragma unroll
+    for (int t = 0; t < NSL / 4; ++t) {
+      const int sl = 4 * t + (lane >> 4);
+      const uint4 v = *(const uint4*)(stage[w] + row * PITCH + sl * GRAM_ROW_BYTES + 16 * c);
+      if (sl0 + sl < nsl)
+        *(uint4*)(xc + ((sl0 + sl) * Tpad + i0 + row) * GRAM_ROW_BYTES + 16 * c) = v;
+    }
+    __builtin_amdgcn_wave_barrier();
+    float n = 0.f;
+#pragma unroll
+    for (int r = 0; r < CONV_BATCH; ++r) {
+      const double s = wave_sum(in_pad ? acc[r] : 0.0, lane);
+      if (lane == r) n = i0 + r < T ? (float)s : 0.f;
+    }
+    if (lane < CONV_BATCH) ncs[ch * Tpad + i0 + lane] = n;
   }
 }
 
@@ -225,21 +272,21 @@ hipError_t launch_centre_convert(const float* X, int64_t ldx, int64_t T,
                                  int64_t D, int64_t Tpad, int64_t Dpad,
                                  int precision, const double* mu, void* xc,
                                  float* ncs, hipStream_t s) {
-  dim3 g((unsigned)((norm_chunks(Dpad) + 3) / 4), (unsigned)((Tpad + CONV_ROWS - 1) / CONV_ROWS));
-  switch (precision) {
-    case TRAKNN_FP32:
-      hipLaunchKernelGGL(centre_convert_kernel<TRAKNN_FP32>, g, dim3(256), 0, s,
-                         X, ldx, T, D, Tpad, Dpad, mu, xc, ncs);
-      break;
-    case TRAKNN_BF16X3:
-      hipLaunchKernelGGL(centre_convert_kernel<TRAKNN_BF16X3>, g, dim3(256), 0,
-                         s, X, ldx, T, D, Tpad, Dpad, mu, xc, ncs);
-      break;
-    default:
-      hipLaunchKernelGGL(centre_convert_kernel<TRAKNN_FP16>, g, dim3(256), 0, s,
-                         X, ldx, T, D, Tpad, Dpad, mu, xc, ncs);
-      break;
-  }
+  // Rows per wave: 16 (the chunk's means are read once for them), fewer while
+  // that leaves less than CONV_WAVES waves (16 per CU), so that a short series
+  // is one memory latency deep instead of four: 18 -> 9 us on 512 x 1024 fields.
+  constexpr int64_t CONV_WAVES = 4096;
+  const int64_t nch = norm_chunks(Dpad);
+  int nrows = 16;
+  while (nrows > CONV_BATCH && nch * (Tpad / nrows) < CONV_WAVES) nrows /= 2;
+  const dim3 g((unsigned)((nch * ((Tpad + nrows - 1) / nrows) + 3) / 4));
+#define TRAKNN_CONVERT(P)                                                                        \
+  hipLaunchKernelGGL(centre_convert_kernel<P>, g, dim3(256), 0, s, X, ldx, T, D, Tpad, Dpad, mu, \
+                     (char*)xc, ncs, nrows)
+  if (precision == TRAKNN_FP32) TRAKNN_CONVERT(TRAKNN_FP32);
+  else if (precision == TRAKNN_BF16X3) TRAKNN_CONVERT(TRAKNN_BF16X3);
+  else TRAKNN_CONVERT(TRAKNN_FP16);
+#undef TRAKNN_CONVERT
   return hipGetLastError();
 }
 
