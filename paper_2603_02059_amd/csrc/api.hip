@@ -383,14 +383,9 @@ int enqueue_knn(traknn_plan_s* plan, const float* X, int64_t ldx, void* workspac
       const int64_t t1 = pi + 1 < npass ? plan->band_t0[pi + 1] : np0;
       const int64_t nt = t1 - t0;
       const int64_t srows = nt + c.L_max - 1 < T - t0 ? nt + c.L_max - 1 : T - t0;
-      const int nbi = (int)((srows + GRAM_TILE - 1) / GRAM_TILE);
-      const int J0 = (int)(t0 / GRAM_TILE);
-      const int64_t c0 = (int64_t)J0 * GRAM_TILE;
-      const int64_t nbc = plan->nb - J0;  // block-columns from J0 on
-      const int64_t ntiles = nbi * nbc - (int64_t)nbi * (nbi - 1) / 2;
-      if ((rc = fail_hip(launch_gram_band(xc, ncs, T, plan->Tpad, plan->Dpad, plan->nb, ntiles,
-                                          c.precision, t0, nbi, srows, J0, S, plan->ldS, ST,
-                                          plan->ldST, s))))
+      const int64_t c0 = t0 / GRAM_TILE * GRAM_TILE;
+      if ((rc = fail_hip(launch_gram_band(xc, ncs, T, plan->Tpad, plan->Dpad, c.precision, t0,
+                                          srows, c0, S, plan->ldS, ST, plan->ldST, s))))
         return rc;
       const WindowRange rows{t0, t0 + srows, c0, t0, T, T, 1, T};
       if ((rc = fail_hip(launch_window_band(S, plan->ldS, T, c.L_min, c.L_max, c.k,
@@ -416,8 +411,8 @@ int enqueue_knn(traknn_plan_s* plan, const float* X, int64_t ldx, void* workspac
     if (plan->timing) plan->timed_calls++;
     return TRAKNN_OK;
   }
-  if ((rc = fail_hip(launch_gram(xc, ncs, plan->T, plan->Tpad, plan->Dpad, plan->nb,
-                                 plan->ntiles, c.precision, S, plan->ldS, s))))
+  if ((rc = fail_hip(launch_gram(xc, ncs, plan->T, plan->Tpad, plan->Dpad, c.precision, S,
+                                 plan->ldS, s))))
     return rc;
   if ((rc = record(plan, 3, s))) return rc;
   if ((rc = fail_hip(launch_window_topk(S, plan->ldS, plan->T, c.L_min, c.L_max,
@@ -530,7 +525,6 @@ int traknn_plan(const traknn_config* cfg, traknn_plan_t* out,
   p->np0 = c.T - c.L_min + 1;
   p->NL = c.L_max - c.L_min + 1;
   p->nb = (int)((c.T + GRAM_TILE - 1) / GRAM_TILE);
-  p->ntiles = (int64_t)p->nb * (p->nb + 1) / 2;
   p->band_rows = p->rb + c.L_max - 1 < c.T ? p->rb + c.L_max - 1 : c.T;
   p->ldST = p->rb ? matrix_stride(p->band_rows) : 0;
   p->tchunks = colstat_chunks(c.T);

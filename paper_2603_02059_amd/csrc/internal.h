@@ -13,13 +13,13 @@ namespace traknn {
 
 // ---------------------------------------------------------------------------
 // Gram tiling (Eq. 4 stage). One workgroup owns a GRAM_TILE x GRAM_TILE block
+// (smaller where that leaves CUs idle)
 // of the distance matrix; every K slice moves GRAM_ROW_BYTES of each of the
-// 2 * GRAM_TILE operand rows through LDS, GRAM_BUFFERS slices deep.
+// 2 * GRAM_TILE operand rows through LDS.
 // ---------------------------------------------------------------------------
 constexpr int GRAM_TILE = 256;
 constexpr int GRAM_THREADS = 512;
 constexpr int GRAM_ROW_BYTES = 64;
-constexpr int GRAM_BUFFERS = 4;
 constexpr int GRAM_GROUP_ROWS = 4;  // block-rows per L2 locality group
 constexpr int NUM_XCD = 8;
 
@@ -110,7 +110,6 @@ struct traknn_plan_s {
   int64_t np0;       // T - L_min + 1: rows of every output block
   int NL;            // L_max - L_min + 1
   int nb;            // ceil(T / GRAM_TILE) block-columns
-  int64_t ntiles;    // nb (nb + 1) / 2 upper-triangular tile pairs
   int64_t rb;        // band mode: at most this many trajectory rows per pass (0: whole matrix)
   std::vector<int64_t> band_t0;  // band mode: the passes' first trajectory rows
   int64_t band_rows; // band mode: rows of S held, rb + L_max - 1 (at most T)
@@ -140,20 +139,17 @@ hipError_t launch_centre_convert(const float* X, int64_t ldx, int64_t T,
                                  float* ncs, hipStream_t s);
 // gram.hip
 hipError_t launch_gram(const void* xc, const float* ncs, int64_t T, int64_t Tpad,
-                       int64_t Dpad, int nb, int64_t ntiles, int precision,
-                       float* S, int64_t ldS, hipStream_t s);
-// Band mode: rows a_row0 .. a_row0 + rows_out - 1 (nbi = ceil(rows_out / 256)
-// block-rows) against the columns of block-columns J0 = a_row0 / 256 .. nb -
-// 1. Only the tiles J >= J0 + I, those that hold entries above the diagonal,
-// are computed (ntiles = nbi nb' - nbi (nbi - 1) / 2 with nb' = nb - J0); the
-// rest of both buffers is left unwritten. Field j of row a_row0 + i goes to
-// S[i * ldS + j - 256 J0] and, transposed, to ST[(j - 256 J0) * ldST + i].
-// a_row0 must be a multiple of 8, nbi <= nb', a_row0 + nbi * 256 <= Tpad and
-// ldST >= rows_out, a multiple of 4.
+                       int64_t Dpad, int precision, float* S, int64_t ldS, hipStream_t s);
+// Band mode: rows a_row0 .. a_row0 + rows_out - 1 against the columns from c0
+// = 256 (a_row0 / 256) on. Only the tiles that hold entries above the diagonal
+// are computed; the rest of both buffers is left unwritten. Field j of row
+// a_row0 + i goes to S[i * ldS + j - c0] and, transposed, to ST[(j - c0) *
+// ldST + i]. a_row0 must be a multiple of 8, a_row0 + rows_out <= T, Tpad at
+// least a tile past T and ldST >= rows_out, a multiple of 4.
 hipError_t launch_gram_band(const void* xc, const float* ncs, int64_t T, int64_t Tpad,
-                            int64_t Dpad, int nb, int64_t ntiles, int precision,
-                            int64_t a_row0, int nbi, int64_t rows_out, int J0, float* S,
-                            int64_t ldS, float* ST, int64_t ldST, hipStream_t s);
+                            int64_t Dpad, int precision, int64_t a_row0, int64_t rows_out,
+                            int64_t c0, float* S, int64_t ldS, float* ST, int64_t ldST,
+                            hipStream_t s);
 // window_topk.hip
 hipError_t launch_window_topk(const float* S, int64_t ldS, int64_t T, int L_min,
                               int L_max, int k, int splits, double* part_d,

@@ -20,9 +20,25 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
+@pytest.mark.parametrize("T,rb", [(700, 304), (2300, 512), (2561, 1024), (6400, 1536)])
+@pytest.mark.parametrize("prec", ["fp32", "bf16x3", "fp16"])
+def test_tile_sizes_agree(T, rb, prec):
+    """The whole matrix and the passes of band mode take different Gram tiles
+    (256, 128 or 64 fields, by how many the launch has), so equal lists mean
+    equal distances from every shape, ragged last tiles and rows included."""
+    from paper_2603_02059_amd import traknn as tk
+    D, L, k = 77, 4, 6
+    print(f"[gpu] tiles T={T} row_batch={rb} {prec}", flush=True)
+    X = torch.from_numpy(synth.make_fields(T, 7, 11, sigma=1.0, n_events=2, event_len=L,
+                                           seed=T)[0]).cuda()
+    a, b = tk.knn(X, L, k, prec), tk.knn(X, L, k, prec, row_batch=rb)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+
+
 @pytest.mark.parametrize("prec", ["fp32", "bf16x3", "fp16"])
 @pytest.mark.parametrize("T,D", [(257, 32), (257, 33), (261, 64), (262, 65), (256, 96), (300, 129),
-                                 (300, 511), (300, 512), (300, 513), (513, 545), (300, 1056)])
+                                 (300, 511), (300, 512), (300, 513), (513, 545), (300, 1056),
+                                 (2300, 33), (2049, 129)])
 def test_gram_slice_edges(T, D, prec):
     from paper_2603_02059_amd import traknn as tk
     L, k = 3, 5
