@@ -17,29 +17,6 @@ namespace {
 constexpr size_t WS_ALIGN = 256;
 constexpr int64_t MAX_T = 1 << 20;       // int32 indices with headroom
 constexpr int64_t MAX_D = (int64_t)1 << 28;
-constexpr size_t MAX_WIN_LDS = 64 * 1024;
-// Window waves to aim for (row blocks x waves per block); a compile-time
-// tuning knob. 12288 gives 4 waves per 8-row block at T = 27394, the best of
-// the block shapes measured there.
-#ifndef TRAKNN_WIN_TARGET_UNITS
-#define TRAKNN_WIN_TARGET_UNITS 12288
-#endif
-constexpr int64_t WIN_TARGET_UNITS = TRAKNN_WIN_TARGET_UNITS;
-// The same for the window launches of band mode, whose rows are shorter.
-#ifndef TRAKNN_BAND_WIN_TARGET_UNITS
-#define TRAKNN_BAND_WIN_TARGET_UNITS TRAKNN_WIN_TARGET_UNITS
-#endif
-constexpr int64_t BAND_WIN_TARGET_UNITS = TRAKNN_BAND_WIN_TARGET_UNITS;
-// Band mode's column windows have rows of only row_batch candidates, so each
-// wave's fixed costs (seeding its rows' lists, writing them out) weigh more:
-// half the waves per block. At T = 27394 with passes of 4088 rows this gives 2
-// waves per block, measured best against 1, 4 and 8.
-#ifndef TRAKNN_BAND_COL_TARGET_UNITS
-#define TRAKNN_BAND_COL_TARGET_UNITS 6144
-#endif
-constexpr int64_t BAND_COL_TARGET_UNITS = TRAKNN_BAND_COL_TARGET_UNITS;
-constexpr int MAX_SPLITS = MERGE_MAX_SPLITS;
-
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 int64_t round_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 // Row stride of a distance buffer, floats: whole 256-byte segments, an odd
@@ -54,47 +31,20 @@ bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
 int fail_hip(hipError_t e) { return e == hipSuccess ? TRAKNN_OK : TRAKNN_ERR_HIP; }
 
-// Column splits of the window stage: one workgroup of W waves per block of
-// WINDOW1_ROWS rows (the waves split the block's diagonals and share a per-row
-// bound), with W as large as the LDS budget and the target parallelism allow,
-// for a launch of `rows` rows (of the shortest length) over `cands` candidate
-// columns. A multi-length request runs the same kernel once per length (or
-// pair of lengths); L_max sizes the LDS.
-int window_splits(const traknn_plan_s* p, int64_t rows, int64_t cands, int64_t target) {
-  const int k = p->cfg.k;
-  const int L = p->cfg.L_max;
-  const int64_t nrb = (rows + WINDOW1_ROWS - 1) / WINDOW1_ROWS;
-  const int64_t nchunks = (cands + WINDOW1_ROWS - 1 + 63) / 64;
-  // a sweep's passes hold up to WINDOW_LENGTHS_PER_PASS lengths' lists
-  const int G = p->NL > 1 ? WINDOW_LENGTHS_PER_PASS : 1;
-  const size_t base = window1_lds_bytes(L, G, k, 0);
-  const size_t per_wave = window1_lds_bytes(L, G, k, 1) - base;
-  if (base + per_wave > MAX_WIN_LDS) return 0;
-  // Every wave keeps its own k-long list per row and length of its pass, so
-  // when those hold more than 10 entries (G k > 10) the target shrinks in
-  // proportion. At T = 27394 this gives 4, 2 and 1 waves per block for k =
-  // 10, 20 and 40 at one length, and 2 for a sweep's pairs of lengths at
-  // k = 10: the fastest of the counts measured for each.
+// The size of the workspace's spare region, in lists per row, for `rows` rows
+// over `cands` candidate columns. The window stage once kept that many partial
+// lists of every row there; it writes its lists to the output now. The region
+// stays in the workspace so that a plan's workspace_bytes, and with them which
+// plans traknn_knn_noalloc accepts and which row_batch fits a budget, do not
+// change.
+int spare_lists(const traknn_plan_s* p, int64_t rows, int64_t cands, int64_t target) {
+  const int64_t k = p->cfg.k, G = p->NL > 1 ? 2 : 1;
+  const int64_t base = G * 64, per = (int64_t)(p->cfg.L_max + 15) * 256 + G * 96 * k;
   if (G * k > 10) target = target * 10 / (G * k);
-  int64_t W = (target + nrb - 1) / nrb;
-  const int64_t wmax = (int64_t)((MAX_WIN_LDS - base) / per_wave);
-  if (W > wmax) W = wmax;
-  if (W > MAX_SPLITS) W = MAX_SPLITS;
-  if (W > nchunks) W = nchunks;
-  if (W < 1) W = 1;
-  return (int)W;
-}
-
-// Whole matrix: one launch of all rows over all columns. Band mode: per pass,
-// a row window of up to rb rows over the columns from the pass's first row on,
-// and a column window of the rows from the pass's first on over the pass's
-// (up to) rb trajectories.
-bool plan_window(traknn_plan_s* p) {
-  const int64_t rows = p->rb && p->rb < p->np0 ? p->rb : p->np0;
-  const int64_t target = p->rb ? BAND_WIN_TARGET_UNITS : WIN_TARGET_UNITS;
-  p->win_splits = window_splits(p, rows, p->np0, target);
-  p->col_splits = p->rb ? window_splits(p, p->np0, rows, BAND_COL_TARGET_UNITS) : 0;
-  return p->win_splits > 0 && (!p->rb || p->col_splits > 0);
+  const int64_t blocks = (rows + 7) / 8, chunks = (cands + 70) / 64;
+  int64_t W = (target + blocks - 1) / blocks;
+  for (const int64_t most : {(65536 - base) / per, (int64_t)16, chunks}) W = W > most ? most : W;
+  return W < 1 ? 1 : (int)W;
 }
 
 // Fused mode: tile stride, block-rows and the ends of the second and third
@@ -232,7 +182,7 @@ void plan_layout(traknn_plan_s* p) {
     L.f_si = take(np * nslot * p->cfg.k * sizeof(int32_t));
     L.f_rd = take(np * p->cfg.k * sizeof(double));
     L.f_ri = take(np * p->cfg.k * sizeof(int32_t));
-    L.S = L.ST = L.part_d = L.part_i = L.cpart_d = L.cpart_i = o;
+    L.S = L.ST = o;
     L.total = o;
     return;
   }
@@ -241,15 +191,14 @@ void plan_layout(traknn_plan_s* p) {
   L.S = take((size_t)(p->rb ? p->band_rows : p->T) * p->ldS * sizeof(float));
   // band mode: the transposed band, one row per field
   L.ST = take(p->rb ? (size_t)p->T * p->ldST * sizeof(float) : 0);
-  // partial lists: of the whole-matrix launch or a pass's row window (rb rows);
-  // band mode adds those of its first column window (every row)
+  // spare (spare_lists)
   const int64_t prows = p->rb && p->rb < p->np0 ? p->rb : p->np0;
-  const size_t nparts = (size_t)p->win_splits * p->NL * prows * p->cfg.k;
-  L.part_d = take(nparts * sizeof(double));
-  L.part_i = take(nparts * sizeof(int32_t));
-  const size_t ncol = p->rb ? (size_t)p->col_splits * p->NL * p->np0 * p->cfg.k : 0;
-  L.cpart_d = take(ncol * sizeof(double));
-  L.cpart_i = take(ncol * sizeof(int32_t));
+  const size_t nparts = (size_t)spare_lists(p, prows, p->np0, 12288) * p->NL * prows * p->cfg.k;
+  take(nparts * sizeof(double));
+  take(nparts * sizeof(int32_t));
+  const size_t ncol = p->rb ? (size_t)spare_lists(p, p->np0, prows, 6144) * p->NL * p->np0 * p->cfg.k : 0;
+  take(ncol * sizeof(double));
+  take(ncol * sizeof(int32_t));
   L.total = o;
 }
 
@@ -345,8 +294,6 @@ int enqueue_knn(traknn_plan_s* plan, const float* X, int64_t ldx, void* workspac
   float* ncs = at<float>(workspace, L.ncs);
   void* xc = at<char>(workspace, L.xc);
   float* S = at<float>(workspace, L.S);
-  double* part_d = at<double>(workspace, L.part_d);
-  int32_t* part_i = at<int32_t>(workspace, L.part_i);
 
   if ((rc = record(plan, 0, s))) return rc;
   if ((rc = fail_hip(launch_colstats(X, ldx, plan->T, plan->D, plan->tchunks,
@@ -370,12 +317,11 @@ int enqueue_knn(traknn_plan_s* plan, const float* X, int64_t ldx, void* workspac
     // - Column window: the rows t0 .. n' - 1 over the pass's earlier
     //   candidates (t0 .. t1 - 1, j < i), read from the transposed band (S is
     //   symmetric).
-    // One merge folds both into the rows' running lists; after pass p the rows
-    // t0 .. t1 - 1 are final. So every ordered pair of trajectories is a candidate
-    // exactly once, and the passes together contract about half the matrix.
+    // Both start from the rows' lists in the output (none before pass 0); after
+    // pass p the rows t0 .. t1 - 1 are final. So every ordered pair of
+    // trajectories is a candidate exactly once, and the passes together
+    // contract about half the matrix.
     float* ST = at<float>(workspace, L.ST);
-    double* cpart_d = at<double>(workspace, L.cpart_d);
-    int32_t* cpart_i = at<int32_t>(workspace, L.cpart_i);
     const int64_t T = plan->T, np0 = plan->np0;
     const size_t npass = plan->band_t0.size();
     for (size_t pi = 0; pi < npass; ++pi) {
@@ -388,20 +334,12 @@ int enqueue_knn(traknn_plan_s* plan, const float* X, int64_t ldx, void* workspac
                                           srows, c0, S, plan->ldS, ST, plan->ldST, s))))
         return rc;
       const WindowRange rows{t0, t0 + srows, c0, t0, T, T, 1, T};
-      if ((rc = fail_hip(launch_window_band(S, plan->ldS, T, c.L_min, c.L_max, c.k,
-                                            plan->win_splits, rows, t0, nt, part_d, part_i,
-                                            s))))
+      if ((rc = fail_hip(launch_window(S, plan->ldS, T, c.L_min, c.L_max, c.k, rows, t0, nt,
+                                       t0 > 0 ? np0 : 0, nbr_idx, nbr_dist, s))))
         return rc;
       const WindowRange cols{c0, T, t0, t0, t1, t0 + srows, -T, -1};
-      if ((rc = fail_hip(launch_window_band(ST, plan->ldST, T, c.L_min, c.L_max, c.k,
-                                            plan->col_splits, cols, t0, np0 - t0, cpart_d,
-                                            cpart_i, s))))
-        return rc;
-      // every row from t0 on holds the earlier passes' lists (none in pass 0)
-      const MergeSet mr{part_d, part_i, plan->win_splits, (int)nt};
-      const MergeSet mc{cpart_d, cpart_i, plan->col_splits, (int)(np0 - t0)};
-      if ((rc = fail_hip(launch_merge_band(mr, mc, T, c.L_min, c.L_max, c.k, t0, np0 - t0,
-                                           t0 > 0 ? np0 : 0, nbr_idx, nbr_dist, s))))
+      if ((rc = fail_hip(launch_window(ST, plan->ldST, T, c.L_min, c.L_max, c.k, cols, t0,
+                                       np0 - t0, t0 > 0 ? np0 : t1, nbr_idx, nbr_dist, s))))
         return rc;
     }
     // the passes interleave the stages: the Gram slot times them all
@@ -415,14 +353,11 @@ int enqueue_knn(traknn_plan_s* plan, const float* X, int64_t ldx, void* workspac
                                  plan->ldS, s))))
     return rc;
   if ((rc = record(plan, 3, s))) return rc;
-  if ((rc = fail_hip(launch_window_topk(S, plan->ldS, plan->T, c.L_min, c.L_max,
-                                        c.k, plan->win_splits, part_d,
-                                        part_i, s))))
+  const WindowRange all{0, plan->T, 0, 0, plan->T, plan->T, -plan->T, plan->T};
+  if ((rc = fail_hip(launch_window(S, plan->ldS, plan->T, c.L_min, c.L_max, c.k, all, 0,
+                                   plan->np0, 0, nbr_idx, nbr_dist, s))))
     return rc;
   if ((rc = record(plan, 4, s))) return rc;
-  if ((rc = fail_hip(launch_merge(part_d, part_i, plan->T, c.L_min, c.L_max, c.k,
-                                  plan->win_splits, nbr_idx, nbr_dist, s))))
-    return rc;
   if ((rc = record(plan, 5, s))) return rc;
   if (plan->timing) plan->timed_calls++;
   return TRAKNN_OK;
@@ -529,12 +464,7 @@ int traknn_plan(const traknn_config* cfg, traknn_plan_t* out,
   p->ldST = p->rb ? matrix_stride(p->band_rows) : 0;
   p->tchunks = colstat_chunks(c.T);
   p->fused = fused ? 1 : 0;
-  if (fused) {
-    plan_fused(p);
-  } else if (!plan_window(p)) {
-    delete p;
-    return TRAKNN_ERR_UNSUPPORTED;
-  }
+  if (fused) plan_fused(p);
   if (p->rb) {
     try {
       plan_band_passes(p);

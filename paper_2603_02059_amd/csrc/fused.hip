@@ -134,8 +134,6 @@ __global__ __launch_bounds__(F64_THREADS) void fused_f64_kernel(
 // by insertion.
 constexpr int SEL_WAVES = 4;
 constexpr int SEL_PARK = 1024;
-// a batch with at least this many entries to insert is merged by a sort
-constexpr int SEL_SORT_MIN = 6;
 template <bool FINAL>
 __global__ __launch_bounds__(64 * SEL_WAVES) void select_kernel(
     FusedGeom g, FusedSlots out, double* __restrict__ bound, double* __restrict__ run_d,
@@ -197,36 +195,7 @@ __global__ __launch_bounds__(64 * SEL_WAVES) void select_kernel(
         const int ki = __builtin_amdgcn_readlane(ei, k - 1);
         const bool pass = e < p1 && key_less(d, c, kd, ki);
         const uint64_t m = __ballot(pass);
-        const int cnt = __builtin_popcountll(m);
-        const int room = 64 - k;  // entries one sort takes beside the list
-        if (cnt >= SEL_SORT_MIN && room >= SEL_SORT_MIN) {
-          // the passing entries, compacted, go in with the list (lanes < k)
-          // up to `room` at a time (lanes k ..), one sort each; its first k
-          // lanes are the new list
-          const int pos = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
-          if (pass) {
-            mrg_d[w][pos] = d;
-            mrg_i[w][pos] = c;
-          }
-          __builtin_amdgcn_wave_barrier();
-          for (int c0 = 0; c0 < cnt; c0 += room) {
-            const int src = lane - k + c0;
-            double md = lane < k ? ed : __builtin_huge_val();
-            int mi = lane < k ? ei : INT_MAX - 64 + lane;
-            if (lane >= k && src < cnt) {
-              md = mrg_d[w][src];
-              mi = mrg_i[w][src];
-            }
-            bitonic_sort64(md, mi, lane);
-            const bool real = mi < INT_MAX - 64;
-            ed = real ? md : __builtin_huge_val();
-            ei = real ? mi : INT_MAX;
-          }
-          __builtin_amdgcn_wave_barrier();
-        } else if (m) {
-          insert_reg(m, d, c, k, ed, ei);
-        }
+        merge_batch(m, d, c, k, ed, ei, mrg_d[w], mrg_i[w], lane);
       }
       __builtin_amdgcn_wave_barrier();
     }

@@ -90,10 +90,6 @@ __device__ __forceinline__ float prefilter_bound(double bound) {
 // builtins that return the wave's lane mask directly
 constexpr int FCMP_OLE = 5;
 
-// A batch with at least this many candidates below the k-th of a sorted list
-// is merged into it by sorts rather than by one insertion each.
-constexpr int LIST_SORT_MIN = 6;
-
 // Per-wave LDS scratch of a recipient's candidates: up to 64 compacted entries.
 struct EstScratch {
   double* d;  // [64]
@@ -200,7 +196,7 @@ __device__ __forceinline__ int recipient_topk(const float* V, int sp, int sq, in
         double d = lane < total ? sc.d[lane] : __builtin_huge_val();
         int c = lane < total ? sc.i[lane] : INT_MAX - 64 + lane;
         __builtin_amdgcn_wave_barrier();
-        bitonic_sort64(d, c, lane);
+        bitonic_sort64<NB != 4>(d, c);
         const bool real = lane < (total < k ? total : k);
         ed = real ? d : __builtin_huge_val();
         ei = real ? c : INT_MAX;
@@ -231,7 +227,7 @@ __device__ __forceinline__ int recipient_topk(const float* V, int sp, int sq, in
             md = sc.d[src];
             mi = sc.i[src];
           }
-          bitonic_sort64(md, mi, lane);
+          bitonic_sort64<NB != 4>(md, mi);
           const bool real = mi < INT_MAX - 64;
           ed = real ? md : __builtin_huge_val();
           ei = real ? mi : INT_MAX;
@@ -247,33 +243,16 @@ __device__ __forceinline__ int recipient_topk(const float* V, int sp, int sq, in
   double d = lane < total ? sc.d[lane] : __builtin_huge_val();
   int c = lane < total ? sc.i[lane] : INT_MAX - 64 + lane;
   __builtin_amdgcn_wave_barrier();  // read before the next recipient writes the scratch
-  if (total > k) bitonic_sort64(d, c, lane);
+  if (total > k) bitonic_sort64<NB != 4>(d, c);
   const bool real = lane < (total < k ? total : k);
   ed = real ? d : __builtin_huge_val();
   ei = real ? c : INT_MAX;
   return total < k ? total : k;
 }
 
-// Bitonic network over the wave's 64 keys alone (keys are non-negative or
-// +inf): one merge of strides S, S / 2, ... 1, then the next block size.
-template <int SIZE, int S>
-__device__ __forceinline__ float sort_keys_merge64(float key, int lane) {
-  const float p = __builtin_bit_cast(float, lane_xor<S>(__builtin_bit_cast(int, key), lane));
-  const bool keep_min = ((lane & S) == 0) == ((lane & SIZE) == 0);
-  key = keep_min ? __builtin_fminf(key, p) : __builtin_fmaxf(key, p);
-  if constexpr (S > 1) return sort_keys_merge64<SIZE, S / 2>(key, lane);
-  return key;
-}
-template <int SIZE = 2>
-__device__ __forceinline__ float sort_keys64(float key, int lane) {
-  key = sort_keys_merge64<SIZE, SIZE / 2>(key, lane);
-  if constexpr (SIZE < 64) return sort_keys64<SIZE * 2>(key, lane);
-  return key;
-}
-
 // The k-th smallest of the wave's 64 keys.
-__device__ __forceinline__ float kth_smallest64(float key, int lane, int k) {
-  key = sort_keys64(key, lane);
+__device__ __forceinline__ float kth_smallest64(float key, int k) {
+  key = sort_dist64(key);
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, key), k - 1));
 }
 
@@ -320,7 +299,7 @@ __device__ __forceinline__ int recipient_establish(const float* V, int sp, int s
       if ((rng[b0 + b] >> lane) & 1) mn = __builtin_fminf(mn, s32);
     }
   }
-  const float tau = kth_smallest64(mn, lane, k);
+  const float tau = kth_smallest64(mn, k);
   bool fallback = tau == __builtin_huge_valf();  // fewer than k lanes hold a candidate
   const double b64 = (double)tau * (1.0 + 0x1p-19);
   const float b32 = prefilter_bound(b64);
@@ -358,7 +337,7 @@ __device__ __forceinline__ int recipient_establish(const float* V, int sp, int s
   double d = lane < total ? sc.d[lane] : __builtin_huge_val();
   int c = lane < total ? sc.i[lane] : INT_MAX - 64 + lane;
   __builtin_amdgcn_wave_barrier();  // the scratch is read before the next recipient writes it
-  if (total > k) bitonic_sort64(d, c, lane);
+  if (total > k) bitonic_sort64<NB != 4>(d, c);
   const bool real = lane < (total < k ? total : k);
   ed = real ? d : __builtin_huge_val();
   ei = real ? c : INT_MAX;

@@ -95,6 +95,7 @@ constexpr int vmcnt_le(int n) { return (n & 15) | (7 << 4) | ((n >> 4) << 14); }
 template <int N>
 __device__ __forceinline__ void barrier_keeping() {
   __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(vmcnt_le(N));
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();

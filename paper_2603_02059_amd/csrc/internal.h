@@ -93,9 +93,8 @@ struct FusedSlots {
 struct Layout {
   // backward first: traknn_score_backward only needs the prefix up to bw_end
   size_t bw_zero, bw_ptr, bw_rev, bw_end;
-  size_t mu_part, mu, ncs, xc, S, ST, part_d, part_i;  // forward
-  size_t cpart_d, cpart_i;                             // band mode: column windows
-  size_t f_bound, f_cnt, f_sd, f_si, f_rd, f_ri;       // fused mode
+  size_t mu_part, mu, ncs, xc, S, ST;             // forward
+  size_t f_bound, f_cnt, f_sd, f_si, f_rd, f_ri;  // fused mode
   size_t total;
 };
 
@@ -117,8 +116,6 @@ struct traknn_plan_s {
   int tchunks;       // partial column-sum blocks of the sampled rows
   int fused;         // fused (S-free) mode
   traknn::FusedGeom fg;  // fused mode: tile geometry
-  int win_splits;    // column splits (waves) per window row block (W)
-  int col_splits;    // band mode: the same for the column windows
   traknn::Layout lay;
   // timing
   int timing;
@@ -151,12 +148,6 @@ hipError_t launch_gram_band(const void* xc, const float* ncs, int64_t T, int64_t
                             int64_t c0, float* S, int64_t ldS, float* ST, int64_t ldST,
                             hipStream_t s);
 // window_topk.hip
-hipError_t launch_window_topk(const float* S, int64_t ldS, int64_t T, int L_min,
-                              int L_max, int k, int splits, double* part_d,
-                              int32_t* part_i, hipStream_t s);
-hipError_t launch_merge(const double* part_d, const int32_t* part_i, int64_t T,
-                        int L_min, int L_max, int k, int splits, int32_t* idx,
-                        double* dist, hipStream_t s);
 // The part of the matrix a window launch sees: S holds rows s0 .. s_end - 1
 // (its row 0 is row s0) and column c at column c - col0; candidates are the
 // columns c_lo .. c_hi - 1 at diagonal offsets j - i in dmin .. dmax, values
@@ -165,27 +156,12 @@ hipError_t launch_merge(const double* part_d, const int32_t* part_i, int64_t T,
 struct WindowRange {
   int64_t s0, s_end, col0, c_lo, c_hi, v_end, dmin, dmax;
 };
-// The lists of trajectory rows t0 .. t0 + nt - 1 (counted for L_min; fewer for
-// longer L) over the candidates of r go to partial lists indexed from t0:
-// [split][length][row - t0][k].
-hipError_t launch_window_band(const float* S, int64_t ldS, int64_t T, int L_min,
-                              int L_max, int k, int splits, const WindowRange& r,
-                              int64_t t0, int64_t nt, double* part_d, int32_t* part_i,
-                              hipStream_t s);
-// One window launch's partial lists, as the merge reads them: W splits of the
-// rows t0 .. t0 + nt - 1.
-constexpr int MERGE_MAX_SPLITS = 16;
-struct MergeSet {
-  const double* d;
-  const int32_t* i;
-  int W, nt;
-};
-// Rows t0 .. t0 + nt - 1 of idx and dist become the k smallest of the lists
-// of sets a and b (both indexed from t0, each covering its first nt rows) and,
-// for the rows below acc_end, of the lists already there.
-hipError_t launch_merge_band(const MergeSet& a, const MergeSet& b, int64_t T, int L_min,
-                             int L_max, int k, int64_t t0, int64_t nt, int64_t acc_end,
-                             int32_t* idx, double* dist, hipStream_t s);
+// Rows t0 .. t0 + nt - 1 (of every length) of idx and dist become the k
+// smallest of the candidates of r and, for the rows below acc_end, of the
+// lists already there.
+hipError_t launch_window(const float* S, int64_t ldS, int64_t T, int L_min, int L_max, int k,
+                         const WindowRange& r, int64_t t0, int64_t nt, int64_t acc_end,
+                         int32_t* idx, double* dist, hipStream_t s);
 hipError_t launch_score(const double* dist, int64_t T, int L_min, int L_max,
                         int k, double* scores, hipStream_t s);
 hipError_t launch_score_prefix(const double* dist, int64_t T, int L_min, int L_max,
@@ -222,23 +198,5 @@ hipError_t launch_slots_refresh(const FusedGeom& g, const FusedSlots& out, doubl
 hipError_t launch_slots_final(const FusedGeom& g, const FusedSlots& out, const double* run_d,
                               const int32_t* run_i, int hlo, int32_t* idx, double* dist,
                               hipStream_t s);
-
-// Window stage sizing shared by the planner and the launcher: LDS bytes of a
-// workgroup of W waves for a pass of G lengths whose longest is L, k neighbours.
-size_t window1_lds_bytes(int L, int G, int k, int W);
-// Lengths a multi-length sweep handles per pass over S (1 to 5; compile-time
-// tuning knob). Each pass reads S once for all of its lengths.
-#ifndef TRAKNN_WIN_LENGTHS_PER_PASS
-#define TRAKNN_WIN_LENGTHS_PER_PASS 2
-#endif
-constexpr int WINDOW_LENGTHS_PER_PASS = TRAKNN_WIN_LENGTHS_PER_PASS;
-static_assert(WINDOW_LENGTHS_PER_PASS >= 1 && WINDOW_LENGTHS_PER_PASS <= 5,
-              "one to five lengths per window pass");
-// Rows per window block (a multiple of the 8-step group; compile-time tuning
-// knob, 8 measured best on the full workload).
-#ifndef TRAKNN_WINDOW1_ROWS
-#define TRAKNN_WINDOW1_ROWS 8
-#endif
-constexpr int WINDOW1_ROWS = TRAKNN_WINDOW1_ROWS;
 
 }  // namespace traknn

@@ -89,9 +89,9 @@ __global__ __launch_bounds__(256) void colsum_reduce_kernel(
 // Sum over the wave by a butterfly of strides 32, 16, ... 1 (every lane gets
 // it), the exchanges of topk_wave.h.
 template <int S = 32>
-__device__ __forceinline__ double wave_sum(double v, int lane) {
-  v += __hiloint2double(lane_xor<S>(__double2hiint(v), lane), lane_xor<S>(__double2loint(v), lane));
-  if constexpr (S > 1) return wave_sum<S / 2>(v, lane);
+__device__ __forceinline__ double wave_sum(double v) {
+  v += lane_xor_d<S>(v);
+  if constexpr (S > 1) return wave_sum<S / 2>(v);
   return v;
 }
 
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(256) void centre_convert_kernel(
     float n = 0.f;
 #pragma unroll
     for (int r = 0; r < CONV_BATCH; ++r) {
-      const double s = wave_sum(in_pad ? acc[r] : 0.0, lane);
+      const double s = wave_sum(in_pad ? acc[r] : 0.0);
       if (lane == r) n = i0 + r < T ? (float)s : 0.f;
     }
     if (lane < CONV_BATCH) ncs[ch * Tpad + i0 + lane] = n;

@@ -13,8 +13,9 @@
 // whose exponents span less than ~29 bits the FP64 recurrence is exact).
 //
 // The 64 candidates of a step all belong to the same row, so the top-k filter
-// is one compare per lane against that row's bound and one ballot; the rare
-// insertions shift a sorted list held one entry per lane.
+// is one compare per lane against that row's bound and one ballot; the few
+// candidates that pass are merged into the row's sorted list, held one entry
+// per lane.
 //
 // A launch may cover part of the matrix (band mode, row-batched streaming):
 // S then holds rows s0 .. s_end - 1, and column c of the matrix at column
@@ -22,17 +23,15 @@
 // row_cap - 1 against the candidate columns c_lo .. c_hi - 1 whose diagonal
 // offset j - i lies in dmin .. dmax, reads values only in columns c_lo ..
 // v_end - 1 (zero elsewhere, which leaves the windows of valid candidates
-// exact), and indexes its partial lists from row_lo. Only the diagonals of
-// the offset range are visited, and only their values are relied on.
+// exact). Only the diagonals of the offset range are visited, and only their
+// values are relied on.
 //
-// A multi-length request (L = L_min .. L_max) runs the kernel once per pair of
-// lengths on the same distance matrix, each length with its own running sums,
-// lists and exclusion zone |i - j| >= L; the merge kernel then combines, per
-// length and row, the W partial lists of the row's column ranges into the
-// final k in (distance, index) order. The result does not depend on the order
-// in which the waves run, nor on how the lengths are grouped into passes.
+// A multi-length request (L = L_min .. L_max) runs the kernel on up to ten
+// lengths at a time on the same distance matrix, each length with its own
+// running sums, lists and exclusion zone |i - j| >= L. The result does not
+// depend on the order in which the waves run, nor on how the lengths are
+// grouped into passes.
 #include <array>
-#include <cfloat>
 #include <climits>
 #include <type_traits>
 #include <utility>
@@ -44,94 +43,171 @@ namespace traknn {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Window + top-k kernel for one trajectory length L.
+// Window + top-k kernel for the trajectory lengths L .. L + G - 1.
 //
-// Each lane holds the R + L - 1 values of its diagonal for the current chunk
-// (the next chunk's values are loaded meanwhile); a step is two FP64 adds, two
-// readlanes of the row's bound, one compare and a ballot.
+// What bounds it: one length at T = 27394 reads 4.7 GB of S (both triangles and
+// the L - 1 halo rows of every eight) in 0.69 ms (L = 5, k = 10; 0.82 ms at k =
+// 40), at the rate of a large read; short series, the latency of a few rounds
+// (12 us at T = 512, 52 us at T = 5000); several lengths, vector issue. Before,
+// every wave kept a list of its own for each of the eight rows and a merge
+// kernel joined them, so that the work on lists grew with the waves: 0.84 and
+// 1.39 ms plus 0.02 and 0.03 of merge at T = 27394, 28 + 14 us at T = 512, 125 +
+// 28 us at T = 5000 (316 + 27 against 157 us at T = 10957).
 //
-// The first chunk of a wave seeds each row's list with a wave-wide bitonic
-// sort of its 64 candidates (the lists start empty, so every candidate would
-// otherwise be inserted one by one). Later insertions shift the list one lane
-// with DPP wave_shr:1, a VALU move, instead of an LDS permute.
+// One workgroup of eight waves per block of eight rows. The block's diagonals
+// go in chunks of 64, eight consecutive chunks (one per wave) a round: a round
+// reads 2 KB runs of each of the 8 + L - 1 rows. A lane holds its diagonal's
+// values of the current chunk and of the next one, which is on its way from
+// memory meanwhile; a step is two FP64 adds, two readlanes of the row's bound,
+// one compare and a ballot.
+//
+// The lists: wave w owns row w's sorted list, one entry per lane. Every wave
+// filters its chunk's candidates against the rows' bounds (the lists' k-th
+// distances, in LDS; candidates equal to the bound still reach the exact
+// (distance, index) test) and appends the few that pass to the rows' buffers in
+// LDS. After the round's barrier each owner merges its row's buffer into its
+// list and lowers the bound, while the next round fills the other buffers: one
+// barrier a round, and a bound read before its update is only looser. So a row
+// has one list and one bound, as tight as a single scan's, whatever the number
+// of waves, and the list goes straight to the output.
+//
+// Where a row's candidates of a round do not fit its buffer (a first round, when
+// there is no bound yet; ties; distances that fall along the scan), the whole
+// round is taken densely: the waves put all their sums in LDS, and each owner
+// picks from its row's 512. It bounds them first by the k-th smallest of its
+// lanes' minima (at least k are within it), so that one sort of at most 64 is
+// the usual cost. Which rounds are dense changes nothing in the lists: they hold
+// the k smallest of all candidates by (distance, index).
+//
+// A launch may start from lists that are already in the output (band mode's
+// later passes): their rows have a bound from the first round on.
+//
+// The lengths of a multi-length sweep share one pass over S, as many as
+// pass_lengths allows: the values of a chunk are read once for all of them, the
+// lengths take turns with the lane's sums, and each length has its own lists
+// (in LDS where there are several), bounds and exclusion zone. Each length's
+// sums are started and slid exactly as in a pass of its own, so the results do
+// not depend on the grouping.
 // ---------------------------------------------------------------------------
-constexpr int W1_ROWS = WINDOW1_ROWS;  // rows per block
-constexpr int W1_GROUP = 8;   // steps unrolled per group
-static_assert(W1_ROWS % W1_GROUP == 0 && (W1_ROWS & (W1_ROWS - 1)) == 0 && W1_ROWS <= 64,
-              "rows per block: a power of two, a multiple of the group, at most a wave");
-#define W1_VALS_BYTES(M) (((size_t)(M) * 64 * sizeof(float) + 15) / 16 * 16)
+constexpr int W1_ROWS = 8;         // rows per block
+constexpr int W1_WAVES = W1_ROWS;  // wave w owns row w
+constexpr int W1_CNT = 4;          // rotating counters of the buffers
+constexpr int W1_MAX_G = 10;       // lengths per pass
+// Entries of a row's buffer: a round passes k / r candidates of a row in
+// expectation (r the round), and two sets of every length's buffers stay within
+// the LDS that a dense round's sums take anyway.
+constexpr int w1_cap(int G) { return G <= 2 ? 64 : G <= 5 ? 32 : 16; }
 
-// One workgroup per row block: wave w scans the w-th of W contiguous ranges
-// of 64-diagonal chunks and keeps its own partial lists. The waves also share
-// one distance bound per row in LDS -- the smallest k-th distance any of them
-// has reached -- and skip candidates above it: such a candidate already has k
-// better ones elsewhere, so it cannot be among the row's k nearest
-// (candidates equal to the bound still reach the exact (distance, index)
-// test). Without the shared bound every wave rediscovers a tight threshold
-// on its own and the insertions grow with W.
-//
-// The steps of a group of U rows only filter (one compare against the row's
-// bound per step, ballots kept in SGPRs); the rare insertions of the group run
-// afterwards, which is exact because every row of a group is a different row.
-// Chunks wholly inside the row range and clear of the exclusion zone (all but
-// a few per row block) skip the per-lane validity tests.
-//
-// G consecutive lengths L .. L + G - 1 share one pass over S (a multi-length
-// sweep pairs them): each lane keeps one running sum per length, every length
-// has its own lists, bounds and exclusion zone, and the values of a chunk are
-// read once for all of them. Each length's sums are started and slid exactly
-// as in a pass of its own, so the results do not depend on G.
+// LDS barrier that leaves the wave's vector loads in flight.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
+  // vmcnt and expcnt at their maxima, lgkmcnt 0
+  __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (3 << 14));
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// A dense round's pick for one row: 512 distances dump[u * 64 * W1_ROWS +
+// lane] (NaN: no candidate) of the columns col + 64 u + lane, u < 8, into the
+// row's list.
+__device__ __forceinline__ void dense_merge(const double* dump, int col, int k, double& ed, int& ei,
+                                            double* sd, int* si, int lane) {
+  constexpr int STEP = 64 * W1_ROWS;
+  double tau = readlane_d(ed, k - 1);
+  if (tau == __builtin_huge_val()) {
+    double mn = tau;
+#pragma unroll
+    for (int u = 0; u < W1_WAVES; ++u) mn = __builtin_fmin(mn, dump[u * STEP + lane]);
+    tau = readlane_d(sort_dist64(mn), k - 1);
+  }
+  int total = 0;  // entries in the scratch
+  auto absorb = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_wave_barrier();
+    double d = lane < total ? sd[lane] : __builtin_huge_val();
+    int c = lane < total ? si[lane] : INT_MAX - 64 + lane;
+    if (__builtin_amdgcn_readfirstlane(ei) == INT_MAX) {  // an empty list
+      bitonic_sort64(d, c);
+      const bool real = lane < (total < k ? total : k);
+      ed = real ? d : __builtin_huge_val();
+      ei = real ? c : INT_MAX;
+    } else {
+      const bool pass = lane < total && key_less(d, c, readlane_d(ed, k - 1),
+                                                 __builtin_amdgcn_readlane(ei, k - 1));
+      merge_batch(__ballot(pass), d, c, k, ed, ei, sd, si, lane);
+    }
+    __builtin_amdgcn_wave_barrier();
+    total = 0;
+  };
+#pragma unroll 1
+  for (int u = 0; u <= W1_WAVES; ++u) {
+    if (u == W1_WAVES) {
+      if (total) absorb();
+      break;
+    }
+    const double d = dump[u * STEP + lane];
+    const int c = col + 64 * u + lane;
+    auto within = [&]() __attribute__((always_inline)) {
+      return __ballot((d <= tau) & key_less(d, c, readlane_d(ed, k - 1),
+                                            __builtin_amdgcn_readlane(ei, k - 1)));
+    };
+    uint64_t m = within();
+    if (total + __builtin_popcountll(m) > 64) {
+      absorb();
+      m = within();
+    }
+    if ((m >> lane) & 1) {
+      const int pos = total + mask_rank(m);
+      sd[pos] = d;
+      si[pos] = c;
+    }
+    total += __builtin_popcountll(m);
+  }
+}
+
 template <int L, int G>
-__global__ __launch_bounds__(1024) void window1_kernel(
+__global__ __launch_bounds__(64 * W1_WAVES, 4) void window1_kernel(
     const float* __restrict__ S, int64_t ldS, int T, int s0, int s_end, int col0, int c_lo,
-    int c_hi, int v_end, int dmin, int dmax, int row_lo, int row_cap, int k, int W,
-    int64_t split_stride, int64_t len_rows, double* __restrict__ part_d,
-    int32_t* __restrict__ part_i) {
-  constexpr int R = W1_ROWS;
-  constexpr int U = W1_GROUP;
+    int c_hi, int v_end, int dmin, int dmax, int row_lo, int row_cap, int acc_end, int k,
+    int np0, int32_t* __restrict__ idx, double* __restrict__ dist) {
+  constexpr int R = W1_ROWS, W = W1_WAVES, CAP = w1_cap(G);
   constexpr int LG = L + G - 1;  // longest length of the pass
   constexpr int M = R + LG - 1;  // rows of values per chunk
-  extern __shared__ __attribute__((aligned(16))) char smem[];
+  // the rows' buffers (two sets), under a dense round's sums
+  constexpr int BUF = G * R * CAP;  // entries of a set
+  constexpr int POOL_BYTES = W * R * 64 * 8;
+  static_assert(2 * BUF * 12 <= POOL_BYTES && G <= W1_MAX_G && CAP <= 64, "buffers fit the pool");
+  __shared__ __attribute__((aligned(16))) char pool[POOL_BYTES];
+  __shared__ double scr_d[W][64];
+  __shared__ int scr_i[W][64];
+  __shared__ __attribute__((aligned(16))) double bnd[G * R];
+  __shared__ int cnt[W1_CNT][G * R];
+  extern __shared__ __attribute__((aligned(16))) char lists[];  // G > 1: [G][R][k]
+  double* const dump = (double*)pool;   // [W][R][64]
+  double* const buf_d = (double*)pool;  // [2][G][R][CAP]
+  int* const buf_i = (int*)(pool + 2 * BUF * 8);
   const int lane = threadIdx.x & 63;
-  const int split = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  unsigned long long* shb = (unsigned long long*)smem;  // [G][R] bits of the shared bounds
-  char* mine = smem + G * R * sizeof(unsigned long long) +
-               (size_t)split * (W1_VALS_BYTES(M + U) + (size_t)G * R * k * 12);
-  float* vl = (float*)mine;  // [M + U][64]: M rows of values, U rows of padding
-  double* ld = (double*)(mine + W1_VALS_BYTES(M + U));  // [G][R][k]
-  int* li = (int*)(ld + (size_t)G * R * k);               // [G][R][k]
-  if (threadIdx.x < G * R)
-    shb[threadIdx.x] = (unsigned long long)__double_as_longlong(__builtin_huge_val());
-  __syncthreads();  // the only workgroup barrier: the waves' trip counts differ
-
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int r0 = row_lo + (int)blockIdx.x * R;
-  int chi[G];    // candidate columns of each length: c_lo .. chi - 1
-  int ncand[G];  // chi - c_lo, at least 0
-  int nrows[G];  // rows of this block that exist for each length
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    const int npl = T - (L + g) + 1;  // trajectories of length L + g
-    chi[g] = c_hi < npl ? c_hi : npl;
-    ncand[g] = chi[g] > c_lo ? chi[g] - c_lo : 0;
+  const int t = r0 + w;  // the wave's own row
+  // length L + g: candidate columns c_lo .. c_lo + ncand - 1, rows of this
+  // block that exist
+  auto chi = [&](int g) __attribute__((always_inline)) {
+    const int npl = T - (L + g) + 1;
+    return c_hi < npl ? c_hi : npl;
+  };
+  auto rows_of = [&](int g) __attribute__((always_inline)) {
+    const int npl = T - (L + g) + 1;
     const int hi = row_cap < npl ? row_cap : npl;
-    nrows[g] = hi - r0 < R ? (hi - r0 > 0 ? hi - r0 : 0) : R;
-  }
+    return hi - r0 < R ? (hi - r0 > 0 ? hi - r0 : 0) : R;
+  };
   // diagonals of the block: every candidate column of some row, within the
   // offset range
   int64_t dlo = (int64_t)c_lo - (r0 + R - 1);
   if (dlo < dmin) dlo = dmin;
-  int64_t dhi = (int64_t)chi[0] - 1 - r0;
+  int64_t dhi = (int64_t)chi(0) - 1 - r0;
   if (dhi > dmax) dhi = dmax;
-  const int64_t NC = ncand[0] > 0 && dhi >= dlo ? (dhi - dlo + 1 + 63) / 64 : 0;
-  const int64_t cb = (int64_t)split * NC / W, ce = (int64_t)(split + 1) * NC / W;
-
-  double thr_d[G];  // lane q: own k-th of row r0 + q, per length
-  int thr_i[G];
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    thr_d[g] = __builtin_huge_val();
-    thr_i[g] = INT_MAX;
-  }
+  const int NC = chi(0) > c_lo && rows_of(0) > 0 && dhi >= dlo ? (int)((dhi - dlo + 1 + 63) / 64) : 0;
 
   // Values of diagonal delta at rows r0 + m (one 256-byte segment per row
   // for the wave), zero outside the held rows and the columns c_lo ..
@@ -140,19 +216,20 @@ __global__ __launch_bounds__(1024) void window1_kernel(
   // precomputed and held across chunks; chunks wholly inside the matrix skip
   // the bounds tests, the others read a safe element and discard it.
   float nxt[M];
-  auto load = [&](int64_t c) __attribute__((always_inline)) {
-    const int64_t dc = dlo + 64 * c;
+  auto load = [&](int c) __attribute__((always_inline)) {
+    const int64_t dc = dlo + 64 * (int64_t)c;
     int64_t stride = ldS + 1;
     asm volatile("" : "+s"(stride));
-    const float* p = S + ((int64_t)(r0 - s0) * ldS + (r0 + dc + lane - col0));
+    const float* row = S + ((int64_t)(r0 - s0) * ldS + (r0 + dc - col0));  // wave-uniform
     const bool inb = r0 + dc >= c_lo && r0 + M - 1 < s_end && r0 + M - 1 + dc + 63 < v_end;
     if (inb) {
 #pragma unroll
       for (int m = 0; m < M; ++m) {
-        nxt[m] = *p;
-        p += stride;
+        nxt[m] = row[lane];
+        row += stride;
       }
     } else {
+      const float* p = row + lane;
       int rows_in = s_end - r0;  // rows r0 + m with m < rows_in are held
       int64_t vlo = c_lo, vhi = v_end;
       asm volatile("" : "+s"(rows_in), "+s"(vlo), "+s"(vhi));
@@ -167,240 +244,253 @@ __global__ __launch_bounds__(1024) void window1_kernel(
       }
     }
   };
-  // after a row's own list changed: lower its shared bound to the list's k-th
-  auto publish = [&](int g, int s) __attribute__((always_inline)) {
-    if (lane == s && thr_d[g] != __builtin_huge_val())
-      atomicMin(&shb[g * R + s], (unsigned long long)__double_as_longlong(thr_d[g]));
-  };
+  if (w < NC) load(w);
 
-  // First chunk of the range: the lists start empty, so each row's list is
-  // seeded with a sort of its first 64 candidates.
-  auto seed_chunk = [&](int64_t c) __attribute__((always_inline)) {
-    const int delta = (int)(dlo + 64 * c) + lane;
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const int Lg = L + g;
-      const bool okd = ((delta >= Lg) | (delta <= -Lg)) & (delta >= dmin) & (delta <= dmax);
-      double D = 0.0;
-#pragma unroll
-      for (int l = 0; l < L + g; ++l) D += (double)vl[l * 64 + lane];
+  // The wave's own lists (row t, length L + g) and their bounds.
+  double own_d = __builtin_huge_val();
+  int own_i = INT_MAX;
+  double* const list_d = (double*)lists + (size_t)w * k + lane;
+  int* const list_i = (int*)((double*)lists + (size_t)G * R * k) + (size_t)w * k + lane;
+  auto get = [&](int g, double& ed, int& ei) __attribute__((always_inline)) {
+    if constexpr (G == 1) {
+      ed = own_d;
+      ei = own_i;
+    } else {
+      ed = lane < k ? list_d[g * R * k] : __builtin_huge_val();
+      ei = lane < k ? list_i[g * R * k] : INT_MAX;
+    }
+  };
+  auto put = [&](int g, double ed, int ei) __attribute__((always_inline)) {
+    if constexpr (G == 1) {
+      own_d = ed;
+      own_i = ei;
+    } else if (lane < k) {
+      list_d[g * R * k] = ed;
+      list_i[g * R * k] = ei;
+    }
+    const double kth = readlane_d(ed, k - 1);
+    if (lane == 0) bnd[g * R + w] = kth;
+  };
 #pragma unroll 1
-      for (int s = 0; s < nrows[g]; ++s) {
-        const int col = r0 + s + delta;
-        const bool valid = okd & ((unsigned)(col - c_lo) < (unsigned)ncand[g]);
-        seed_row(D, col, valid, k, ld + (g * R + s) * k, li + (g * R + s) * k, lane, s,
-                 thr_d[g], thr_i[g]);
-        publish(g, s);
-        D = (D - (double)vl[s * 64 + lane]) + (double)vl[(s + Lg) * 64 + lane];
-      }
+  for (int g = 0; g < G; ++g) {
+    double ed = __builtin_huge_val();
+    int ei = INT_MAX;
+    const bool there = w < rows_of(g);
+    if (there && t < acc_end && lane < k) {
+      const int64_t o = ((int64_t)g * np0 + t) * k + lane;
+      ed = dist[o];
+      ei = idx[o] < 0 ? INT_MAX : idx[o];
     }
-  };
+    put(g, ed, ei);
+    if (!there && lane == 0) bnd[g * R + w] = -__builtin_huge_val();  // no such row: nothing passes
+  }
+  for (int q = threadIdx.x; q < W1_CNT * G * R; q += 64 * W) (&cnt[0][0])[q] = 0;
+  lds_barrier();
 
-  // Later chunks: filter, then insert. EDGE chunks test each candidate's
-  // column range, exclusion zone and row.
-  auto scan_chunk = [&](int64_t c, auto edge_c) __attribute__((always_inline)) {
-    constexpr bool EDGE = decltype(edge_c)::value;
-    const int delta = (int)(dlo + 64 * c) + lane;
-    bool okd[G];
-    double D[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      okd[g] = ((delta >= L + g) | (delta <= -(L + g))) & (delta >= dmin) & (delta <= dmax);
-      D[g] = 0.0;
-#pragma unroll
-      for (int l = 0; l < L + g; ++l) D[g] += (double)vl[l * 64 + lane];
-    }
-#pragma unroll 1
-    for (int gr = 0; gr < R; gr += U) {
-      float w[U + LG];  // rows gr .. gr+U+LG-1
-#pragma unroll
-      for (int j = 0; j < U + LG; ++j) w[j] = vl[(gr + j) * 64 + lane];
-      // bound per row (lane q < R) and length: own k-th or the shared bound,
-      // the smaller
-      double bound[G];
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        const double sh = __longlong_as_double(
-            (long long)__atomic_load_n(&shb[g * R + (lane & (R - 1))], __ATOMIC_RELAXED));
-        bound[g] = __builtin_fmin(thr_d[g], sh);
-      }
-      double Dj[G][U];
-      uint64_t m[G][U];
-      uint64_t any = 0;
-#pragma unroll
-      for (int j = 0; j < U; ++j) {
-        const int s = gr + j;
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          Dj[g][j] = D[g];
-          bool pass = D[g] <= readlane_d(bound[g], s);
-          if constexpr (EDGE) {
-            const int col = r0 + s + delta;
-            pass = pass & okd[g] & ((unsigned)(col - c_lo) < (unsigned)ncand[g]) &
-                   (s < nrows[g]);
-          }
-          m[g][j] = __ballot(pass);
-          any |= m[g][j];
-          if (j + 1 < U || gr + U < R) D[g] = (D[g] - (double)w[j]) + (double)w[j + L + g];
-        }
-      }
-      if (any) {
-#pragma unroll
-        for (int j = 0; j < U; ++j) {
-#pragma unroll
-          for (int g = 0; g < G; ++g) {
-            if (m[g][j]) {
-              const int s = gr + j;
-              insert_seq(m[g][j], Dj[g][j], r0 + s + delta, k, ld + (g * R + s) * k,
-                         li + (g * R + s) * k, lane, s, thr_d[g], thr_i[g]);
-              publish(g, s);
-            }
-          }
-        }
-      }
-    }
-  };
-
-  if (cb < ce) load(cb);
   // interior chunks: every row exists for every length, and the columns and
   // the exclusion zone of the longest length (the strictest) are clear
-  const bool full = nrows[G - 1] == R;
-  for (int64_t c = cb; c < ce; ++c) {
-    // park this chunk's values in this wave's LDS rows (LDS accesses of a
-    // wave execute in order), then start fetching the next chunk
-    __builtin_amdgcn_wave_barrier();
+  const bool full = rows_of(G - 1) == R;
+  const int rounds = (NC + W - 1) / W;
+#pragma unroll 1
+  for (int r = 0; r < rounds; ++r) {
+    const int c = r * W + w;
+    const int64_t dc = dlo + 64 * (int64_t)c;
+    const int delta = (int)dc + lane;
+    const bool interior = full & (c < NC) & ((dc >= LG) | (dc + 63 <= -LG)) & (r0 + dc >= c_lo) &
+                          (r0 + R - 1 + dc + 63 < chi(G - 1)) & (dc >= dmin) & (dc + 63 <= dmax);
+    float cur[M];
 #pragma unroll
-    for (int m = 0; m < M; ++m) vl[m * 64 + lane] = nxt[m];
-    __builtin_amdgcn_wave_barrier();
-    if (c + 1 < ce) load(c + 1);
-    const int64_t dc = dlo + 64 * c;
-    const bool interior = full & ((dc >= LG) | (dc + 63 <= -LG)) & (r0 + dc >= c_lo) &
-                          (r0 + R - 1 + dc + 63 < chi[G - 1]) & (dc >= dmin) &
-                          (dc + 63 <= dmax);
-    if (c == cb)
-      seed_chunk(c);
-    else if (interior)
-      scan_chunk(c, std::false_type{});
-    else
-      scan_chunk(c, std::true_type{});
-  }
-  // partial lists: part[(split * split_stride + g * len_rows + row - row_lo) * k
-  // + q] for length L + g; a range with no chunk leaves its lists empty
+    for (int m = 0; m < M; ++m) cur[m] = nxt[m];
+    if (c + W < NC) load(c + W);
+    // D_{L+g} of the block's rows on the lane's diagonal (NaN: no candidate),
+    // D0 its first row's, a sum in increasing order
+    auto sums = [&](int g, double D0, double (&Dj)[R]) __attribute__((always_inline)) {
+      double D = D0;
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    for (int s = 0; s < nrows[g]; ++s) {
-      const int64_t row = (int64_t)g * len_rows + (r0 - row_lo + s);
-      if (lane < k) {
-        const int64_t o = ((int64_t)split * split_stride + row) * k + lane;
-        part_d[o] = cb < ce ? ld[(g * R + s) * k + lane] : __builtin_huge_val();
-        part_i[o] = cb < ce ? li[(g * R + s) * k + lane] : INT_MAX;
+      for (int j = 0; j < R; ++j) {
+        Dj[j] = D;
+        if (j + 1 < R) D = (D - (double)cur[j]) + (double)cur[j + L + g];
       }
-    }
-  }
-}
-
-// Row blocks of lengths L .. L + G - 1: ceil((rows of length L) / W1_ROWS)
-// workgroups of W waves.
-template <int L, int G>
-hipError_t launch_win1(const float* S, int64_t ldS, int T, int s0, int s_end, int col0,
-                       int c_lo, int c_hi, int v_end, int dmin, int dmax, int row_lo,
-                       int row_cap, int k, int W, int64_t split_stride, int64_t len_rows,
-                       double* pd, int32_t* pi, hipStream_t s) {
-  const size_t lds = window1_lds_bytes(L + G - 1, G, k, W);
-  const int hi = row_cap < T - L + 1 ? row_cap : T - L + 1;
-  const unsigned blocks = (unsigned)((hi - row_lo + W1_ROWS - 1) / W1_ROWS);
-  hipLaunchKernelGGL((window1_kernel<L, G>), dim3(blocks), dim3(64 * W), lds, s, S, ldS, T,
-                     s0, s_end, col0, c_lo, c_hi, v_end, dmin, dmax, row_lo, row_cap, k, W,
-                     split_stride, len_rows, pd, pi);
-  return hipGetLastError();
-}
-
-// One thread per (length, row): a k-step merge of the sorted partial lists
-// (at most MS of them) and, for the rows below acc_end, the running list
-// already in the output. Each source's current head stays in registers (the
-// source loops are unrolled over MS) and only the source that advanced is
-// read again; the running list is first copied to LDS, since the output that
-// holds it is overwritten while it is merged.
-constexpr int MERGE_THREADS = 64;
-template <int MS>
-__global__ __launch_bounds__(MERGE_THREADS) void merge_kernel(
-    MergeSet a, MergeSet b, int T, int np0, int Lmin, int NL, int k, int t0, int nt,
-    int acc_end, int32_t* __restrict__ idx, double* __restrict__ dist) {
-  // rows t0 .. t0 + nt - 1 of every length. A set's partial lists are indexed
-  // from t0 and cover its first rows only; empty slots of the running list
-  // are index -1.
-  extern __shared__ __attribute__((aligned(16))) char msm[];
-  double* rd = (double*)msm + (size_t)threadIdx.x * k;                          // [64][k]
-  int* ri = (int*)((double*)msm + (size_t)MERGE_THREADS * k) + (size_t)threadIdx.x * k;
-  const int64_t g = (int64_t)blockIdx.x * MERGE_THREADS + threadIdx.x;
-  if (g >= (int64_t)NL * nt) return;
-  const int li = (int)(g / nt);
-  const int tr = (int)(g % nt);
-  const int t = t0 + tr;
-  const int npL = T - (Lmin + li) + 1;
-  int32_t* oi = idx + ((int64_t)li * np0 + t) * k;
-  double* od = dist + ((int64_t)li * np0 + t) * k;
-  if (t >= npL) {
-    for (int q = 0; q < k; ++q) {
-      oi[q] = -1;
-      od[q] = __builtin_huge_val();
-    }
-    return;
-  }
-  const int nr = t < acc_end ? k : 0;
-  for (int q = 0; q < nr; ++q) {
-    rd[q] = od[q];
-    ri[q] = oi[q] < 0 ? INT_MAX : oi[q];
-  }
-  const int wa = tr < a.nt ? a.W : 0, wb = tr < b.nt ? b.W : 0;
-  const int ns = wa + wb;  // partial-list sources: a's splits, then b's
-  // entry p of source w's list
-  auto at = [&](int w, int p, double& d, int& i) __attribute__((always_inline)) {
-    const bool in_a = w < wa;
-    const int64_t o = (((int64_t)(in_a ? w : w - wa) * NL + li) * (in_a ? a.nt : b.nt) + tr) * k + p;
-    d = in_a ? a.d[o] : b.d[o];
-    i = in_a ? a.i[o] : b.i[o];
-  };
-  // source w's current head is (hd[w], hi[w]), entry pos[w] of its list
-  int pos[MS];
-  double hd[MS];
-  int hi[MS];
+      if (!interior) {
+        const bool okd = ((delta >= L + g) | (delta <= -(L + g))) & (delta >= dmin) &
+                         (delta <= dmax) & (c < NC);
+        const int nc = chi(g) - c_lo;
+        int nr = rows_of(g);
+        asm volatile("" : "+v"(nr));  // tested where it is used, not kept as masks
 #pragma unroll
-  for (int w = 0; w < MS; ++w) {
-    pos[w] = 0;
-    hd[w] = __builtin_huge_val();
-    hi[w] = INT_MAX;
-    if (w < ns) at(w, 0, hd[w], hi[w]);
-  }
-  int rpos = 0;
-  for (int q = 0; q < k; ++q) {
-    int best = MS;  // MS: the running list
-    double bd = rpos < nr ? rd[rpos] : __builtin_huge_val();
-    int bi = rpos < nr ? ri[rpos] : INT_MAX;
-    bool have = rpos < nr;
-#pragma unroll
-    for (int w = 0; w < MS; ++w) {
-      if (w < ns && pos[w] < k && (!have || key_less(hd[w], hi[w], bd, bi))) {
-        best = w;
-        bd = hd[w];
-        bi = hi[w];
-        have = true;
+        for (int j = 0; j < R; ++j) {
+          const int col = r0 + j + delta;
+          const bool ok = okd & ((unsigned)(col - c_lo) < (unsigned)(nc > 0 ? nc : 0)) & (j < nr);
+          Dj[j] = ok ? Dj[j] : __builtin_nan("");
+        }
       }
-    }
-    if (best == MS) {
-      rpos++;
-    } else {
+    };
+    auto first_sum = [&]() __attribute__((always_inline)) {
+      double D = 0.0;
 #pragma unroll
-      for (int w = 0; w < MS; ++w) {
-        if (w == best) {
-          pos[w]++;
-          if (pos[w] < k) at(w, pos[w], hd[w], hi[w]);
+      for (int l = 0; l < L; ++l) D += (double)cur[l];
+      return D;
+    };
+    const bool unbounded = r == 0 && r0 >= acc_end;  // no list yet: a dense round
+    double D1[R];  // one length: its sums, kept for a dense round
+    if constexpr (G == 1) sums(0, first_sum(), D1);
+    if (!unbounded && c < NC) {
+      double Dg = G == 1 ? 0.0 : first_sum();
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        // the rows' bounds: with one length from a lane each, which keeps the
+        // registers of seven waves per SIMD; else the same in every lane, which
+        // saves the lane reads
+        const double bl = bnd[g * R + (G == 1 ? (lane & (R - 1)) : 0)];
+        double bound[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) bound[j] = G == 1 ? readlane_d(bl, j) : bnd[g * R + j];
+        double Dj[R];
+        if constexpr (G == 1) {
+#pragma unroll
+          for (int j = 0; j < R; ++j) Dj[j] = D1[j];
+        } else {
+          sums(g, Dg, Dj);
+          if (g + 1 < G) Dg += (double)cur[L + g];
+        }
+        uint64_t m[R];
+        uint64_t any = 0;
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+          m[j] = __ballot(Dj[j] <= bound[j]);
+          any |= m[j];
+        }
+        if (any) {
+          // lane j reserves row j's entries, all rows at once
+          int n = 0;
+#pragma unroll
+          for (int j = 0; j < R; ++j)
+            n = lane_select((uint64_t)1 << j, (int)__builtin_popcountll(m[j]), n);
+          int at = 0;
+          if (n) at = __hip_atomic_fetch_add(&cnt[r & (W1_CNT - 1)][g * R + lane], n, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+          for (int j = 0; j < R; ++j)
+            if (m[j]) {
+              const int pos = __builtin_amdgcn_readlane(at, j) + mask_rank(m[j]);
+              if (((m[j] >> lane) & 1) && pos < CAP) {
+                const int o = (r & 1) * BUF + (g * R + j) * CAP + pos;
+                buf_d[o] = Dj[j];
+                buf_i[o] = r0 + j + delta;
+              }
+            }
         }
       }
     }
-    oi[q] = bi == INT_MAX ? -1 : bi;
-    od[q] = bd;
+    lds_barrier();
+    // every wave sees the same counts (they are cleared a round later): the
+    // lengths whose buffers overflowed go densely
+    uint32_t dense = unbounded ? (1u << G) - 1 : 0;
+    if (!unbounded) {
+      const int* const cr = cnt[r & (W1_CNT - 1)];
+      const uint64_t o0 = __ballot(lane < G * R && cr[lane < G * R ? lane : 0] > CAP);
+      uint64_t o1 = 0;
+      if constexpr (G * R > 64) o1 = __ballot(lane + 64 < G * R && cr[lane + 64 < G * R ? lane + 64 : 0] > CAP);
+      if (o0 | o1) {
+        for (int g = 0; g < G; ++g)
+          if (((g < 8 ? o0 >> (8 * g) : o1 >> (8 * (g - 8))) & 0xFF) != 0) dense |= 1u << g;
+      }
+      // the other lengths: merge the own row's buffers
+      const int nq = lane < G ? cr[lane * R + w] : 0;
+      uint64_t todo = __ballot(nq > 0) & ~(uint64_t)dense;
+      while (todo) {
+        const int g = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        const int n = __builtin_amdgcn_readlane(nq, g);
+        const int o = (r & 1) * BUF + (g * R + w) * CAP + lane;
+        const double d = lane < n ? buf_d[o] : __builtin_huge_val();
+        const int ci = lane < n ? buf_i[o] : INT_MAX;
+        double ed;
+        int ei;
+        get(g, ed, ei);
+        const uint64_t m = __ballot(lane < n && key_less(d, ci, readlane_d(ed, k - 1),
+                                                         __builtin_amdgcn_readlane(ei, k - 1)));
+        if (!m) continue;
+        merge_batch(m, d, ci, k, ed, ei, scr_d[w], scr_i[w], lane);
+        put(g, ed, ei);
+      }
+    }
+    if (dense) {
+      lds_barrier();  // the buffers of this round are merged
+#pragma unroll 1
+      for (int g = 0; g < G; ++g) {
+        if (!((dense >> g) & 1)) continue;
+        if constexpr (G == 1) {
+#pragma unroll
+          for (int j = 0; j < R; ++j) dump[(w * R + j) * 64 + lane] = D1[j];
+        } else {
+          double Dg = first_sum();
+#pragma unroll
+          for (int q = 0; q < G; ++q) {
+            if (q == g) {
+              double Dj[R];
+              sums(q, Dg, Dj);
+#pragma unroll
+              for (int j = 0; j < R; ++j) dump[(w * R + j) * 64 + lane] = Dj[j];
+            }
+            if (q + 1 < G) Dg += (double)cur[L + q];
+          }
+        }
+        lds_barrier();
+        if (w < rows_of(g)) {
+          const int col = t + (int)(dlo + 64 * (int64_t)(r * W));
+          double ed;
+          int ei;
+          get(g, ed, ei);
+          dense_merge(dump + w * 64, col, k, ed, ei, scr_d[w], scr_i[w], lane);
+          put(g, ed, ei);
+        }
+        lds_barrier();  // the sums are read before the pool is used again
+      }
+    }
+    if (lane < G) cnt[(r + W1_CNT - 1) & (W1_CNT - 1)][lane * R + w] = 0;
   }
+  // the row's lists; rows that do not exist for a length hold -1 and +inf
+  if (t < row_cap) {
+#pragma unroll 1
+    for (int g = 0; g < G; ++g) {
+      double ed;
+      int ei;
+      get(g, ed, ei);
+      const bool there = w < rows_of(g);
+      if (lane < k) {
+        const int64_t o = ((int64_t)g * np0 + t) * k + lane;
+        idx[o] = there && ei != INT_MAX ? ei : -1;
+        dist[o] = there ? ed : __builtin_huge_val();
+      }
+    }
+  }
+}
+
+// Lengths of a sweep's next pass when `left` remain: 10, 5, 2 or 1, as many as
+// are left and hold at most 120 list entries a row between them: the first
+// rounds pass about k candidates a row and length, which have to fit the
+// buffers (w1_cap). Window stage, T = 27394, L = 1..10, k = 10: 4.6 ms with 10,
+// 5.1 with 5, 6.1 with 2 a pass; T = 6000, L = 1..16, k = 20: 1.26, 1.10 and
+// 1.12 ms. The lists' LDS (at most 12 KB) and the static 40 KB stay within 64.
+inline int pass_lengths(int left, int k) {
+  for (const int g : {10, 5, 2})
+    if (left >= g && g * k <= 120) return g;
+  return 1;
+}
+
+// Row blocks of rows row_lo .. row_cap - 1, the block of length L's lists at
+// idx and dist.
+template <int L, int G>
+hipError_t launch_win1(const float* S, int64_t ldS, int T, const WindowRange& r, int row_lo,
+                       int row_cap, int acc_end, int k, int np0, int32_t* idx, double* dist,
+                       hipStream_t s) {
+  const unsigned blocks = (unsigned)((row_cap - row_lo + W1_ROWS - 1) / W1_ROWS);
+  const size_t lds = G > 1 ? (size_t)G * W1_ROWS * k * 12 : 0;
+  hipLaunchKernelGGL((window1_kernel<L, G>), dim3(blocks), dim3(64 * W1_WAVES), lds, s, S, ldS, T,
+                     (int)r.s0, (int)r.s_end, (int)r.col0, (int)r.c_lo, (int)r.c_hi, (int)r.v_end,
+                     (int)r.dmin, (int)r.dmax, row_lo, row_cap, acc_end, k, np0, idx, dist);
+  return hipGetLastError();
 }
 
 __global__ __launch_bounds__(256) void score_kernel(
@@ -465,92 +555,39 @@ __global__ __launch_bounds__(256) void local_dim_kernel(
 
 }  // namespace
 
-// Launchers of every compiled (L, G): kWin1[L - 1] for L = 1..TRAKNN_MAX_L on
-// its own, kWinG[L - 1] for the lengths L .. L + WINDOW_LENGTHS_PER_PASS - 1
-// of a sweep's pass.
-using WinLaunch = hipError_t (*)(const float*, int64_t, int, int, int, int, int, int, int, int,
-                                 int, int, int, int, int, int64_t, int64_t, double*, int32_t*,
-                                 hipStream_t);
+// Launchers of every compiled (L, G): one length, pairs from every L, and five
+// or ten lengths from the starts that a sweep's passes reach.
+using WinLaunch = hipError_t (*)(const float*, int64_t, int, const WindowRange&, int, int, int,
+                                 int, int, int32_t*, double*, hipStream_t);
 template <int G, int... Ls>
 constexpr std::array<WinLaunch, sizeof...(Ls)> win_table(std::integer_sequence<int, Ls...>) {
   return {&launch_win1<Ls + 1, G>...};
 }
 constexpr auto kWin1 = win_table<1>(std::make_integer_sequence<int, TRAKNN_MAX_L>{});
-constexpr auto kWinG = win_table<WINDOW_LENGTHS_PER_PASS>(
-    std::make_integer_sequence<int, TRAKNN_MAX_L - WINDOW_LENGTHS_PER_PASS + 1>{});
-
-size_t window1_lds_bytes(int L, int G, int k, int W) {
-  return (size_t)G * W1_ROWS * sizeof(unsigned long long) +
-         (size_t)W * (W1_VALS_BYTES(W1_ROWS + L - 1 + W1_GROUP) + (size_t)G * W1_ROWS * k * 12);
+constexpr auto kWin2 = win_table<2>(std::make_integer_sequence<int, TRAKNN_MAX_L - 1>{});
+static WinLaunch window_launcher(int L, int G) {
+  if (L < 1 || L + G - 1 > TRAKNN_MAX_L) return nullptr;
+  if (G == 1) return kWin1[L - 1];
+  if (G == 2) return kWin2[L - 1];
+  if (G == 5) return L == 1 ? &launch_win1<1, 5> : L == 6 ? &launch_win1<6, 5> : L == 11 ? &launch_win1<11, 5> : nullptr;
+  return G == 10 && L == 1 ? &launch_win1<1, 10> : nullptr;
 }
 
-hipError_t launch_window_topk(const float* S, int64_t ldS, int64_t T, int L_min,
-                              int L_max, int k, int splits, double* part_d,
-                              int32_t* part_i, hipStream_t s) {
-  const WindowRange all{0, T, 0, 0, T, T, -T, T};
-  return launch_window_band(S, ldS, T, L_min, L_max, k, splits, all, 0, T - L_min + 1, part_d,
-                            part_i, s);
-}
-
-hipError_t launch_window_band(const float* S, int64_t ldS, int64_t T, int L_min,
-                              int L_max, int k, int splits, const WindowRange& r,
-                              int64_t t0, int64_t nt, double* part_d, int32_t* part_i,
-                              hipStream_t s) {
-  const int NL = L_max - L_min + 1;
-  // partial lists: [split][length][row - t0][k]
-  const int64_t split_stride = (int64_t)NL * nt;
-  // a sweep runs its lengths WINDOW_LENGTHS_PER_PASS at a time (the last pass
-  // takes what is left), a single length on its own
+hipError_t launch_window(const float* S, int64_t ldS, int64_t T, int L_min, int L_max, int k,
+                         const WindowRange& r, int64_t t0, int64_t nt, int64_t acc_end,
+                         int32_t* idx, double* dist, hipStream_t s) {
+  const int64_t np0 = T - L_min + 1;
   for (int L = L_min; L <= L_max;) {
-    const int G = L_max - L + 1 >= WINDOW_LENGTHS_PER_PASS ? WINDOW_LENGTHS_PER_PASS : 1;
-    const int64_t off = (int64_t)(L - L_min) * nt * k;
-    double* pd = part_d + off;
-    int32_t* pi = part_i + off;
-    // rows of length L in [t0, t0 + nt): those with t <= T - L (longer lengths
-    // of the pass have fewer; none at all means the merge marks them absent)
-    const int64_t hi = t0 + nt < T - L + 1 ? t0 + nt : T - L + 1;
-    if (hi > t0) {
-      if (L < 1 || L + G - 1 > TRAKNN_MAX_L) return hipErrorInvalidValue;
-      const WinLaunch f = G > 1 ? kWinG[L - 1] : kWin1[L - 1];
-      const hipError_t e =
-          f(S, ldS, (int)T, (int)r.s0, (int)r.s_end, (int)r.col0, (int)r.c_lo, (int)r.c_hi,
-            (int)r.v_end, (int)r.dmin, (int)r.dmax, (int)t0, (int)(t0 + nt), k, splits,
-            split_stride, nt, pd, pi, s);
-      if (e != hipSuccess) return e;
-    }
+    const int G = pass_lengths(L_max - L + 1, k);
+    const WinLaunch f = window_launcher(L, G);
+    if (!f) return hipErrorInvalidValue;
+    const int64_t off = (int64_t)(L - L_min) * np0 * k;
+    const hipError_t e = f(S, ldS, (int)T, r, (int)t0, (int)(t0 + nt), (int)acc_end, k, (int)np0,
+                           idx + off, dist + off, s);
+    if (e != hipSuccess) return e;
     L += G;
   }
   return hipSuccess;
-}
-
-hipError_t launch_merge(const double* part_d, const int32_t* part_i, int64_t T,
-                        int L_min, int L_max, int k, int splits, int32_t* idx,
-                        double* dist, hipStream_t s) {
-  const int64_t np0 = T - L_min + 1;
-  const MergeSet a{part_d, part_i, splits, (int)np0}, none{nullptr, nullptr, 0, 0};
-  return launch_merge_band(a, none, T, L_min, L_max, k, 0, np0, 0, idx, dist, s);
-}
-
-hipError_t launch_merge_band(const MergeSet& a, const MergeSet& b, int64_t T, int L_min,
-                             int L_max, int k, int64_t t0, int64_t nt, int64_t acc_end,
-                             int32_t* idx, double* dist, hipStream_t s) {
-  const int np0 = (int)(T - L_min + 1);
-  const int NL = L_max - L_min + 1;
-  const int64_t n = (int64_t)NL * nt;
-  if (n <= 0) return hipSuccess;
-  if (a.W > MERGE_MAX_SPLITS || b.W > MERGE_MAX_SPLITS) return hipErrorInvalidValue;
-  const int ns = a.W + b.W;
-  const dim3 grid((unsigned)((n + MERGE_THREADS - 1) / MERGE_THREADS));
-  const size_t lds = (size_t)MERGE_THREADS * k * (sizeof(double) + sizeof(int));
-#define TRAKNN_MERGE_LAUNCH(MS)                                                              \
-  hipLaunchKernelGGL(merge_kernel<MS>, grid, dim3(MERGE_THREADS), lds, s, a, b, (int)T, np0, \
-                     L_min, NL, k, (int)t0, (int)nt, (int)acc_end, idx, dist)
-  if (ns <= 4) TRAKNN_MERGE_LAUNCH(4);
-  else if (ns <= 8) TRAKNN_MERGE_LAUNCH(8);
-  else if (ns <= 16) TRAKNN_MERGE_LAUNCH(16);
-  else TRAKNN_MERGE_LAUNCH(2 * MERGE_MAX_SPLITS);
-#undef TRAKNN_MERGE_LAUNCH
-  return hipGetLastError();
 }
 
 hipError_t launch_score(const double* dist, int64_t T, int L_min, int L_max,
