@@ -12,7 +12,10 @@
 // rounded once to FP32; rows that no term touches are written as zeros by the
 // same kernel. No distance value is needed: the
 // derivative of a squared distance is the field difference itself.
+#include <climits>
+
 #include "internal.h"
+#include "topk_wave.h"
 
 namespace traknn {
 namespace {
@@ -97,32 +100,77 @@ __global__ __launch_bounds__(256) void rev_fill_kernel(
   rev[ptr[j] + pos] = t;
 }
 
-// Insertion sort of each reverse bucket by t (buckets hold ~k entries).
-__global__ __launch_bounds__(256) void rev_sort_kernel(const int32_t* __restrict__ ptr,
-                                                       int np, int32_t* __restrict__ rev) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= np) return;
-  const int b = ptr[j], e = ptr[j + 1];
-  for (int i = b + 1; i < e; ++i) {
-    const int32_t v = rev[i];
-    int q = i - 1;
-    while (q >= b && rev[q] > v) {
-      rev[q + 1] = rev[q];
-      --q;
+// Sort each reverse bucket by t, one wave per bucket: up to 64 entries in
+// registers, up to SORT_LDS in the wave's LDS, longer ones where they are, by a
+// bitonic network whose every exchange is ascending (the first step of a merge
+// pairs an element with its mirror image), so that positions past the end act
+// as +inf. Buckets hold k entries on average, but a trajectory near the centre
+// of its data is a neighbour of hundreds: with one thread per bucket (insertion
+// sort) the longest of T = 1461, k = 10 took 205 us, this 6 us.
+constexpr int SORT_LDS = 1024;
+__device__ __forceinline__ void sort_ints(int32_t* v, int n, int lane) {
+  for (int size = 2; size < 2 * n; size <<= 1) {
+    for (int s = size; s > 1; s >>= 1) {  // s == size: the mirror step
+      const int half = s >> 1;
+      for (int p = lane;; p += 64) {
+        const int blk = p / half * s, off = p % half;
+        const int i = blk + off, j = s == size ? blk + s - 1 - off : i + half;
+        if (blk >= n) break;
+        if (j < n) {
+          const int32_t x = v[i], y = v[j];
+          if (y < x) {
+            v[i] = y;
+            v[j] = x;
+          }
+        }
+      }
+      __threadfence_block();
+      __builtin_amdgcn_wave_barrier();
     }
-    rev[q + 1] = v;
+  }
+}
+__global__ __launch_bounds__(256) void rev_sort_kernel(const int32_t* __restrict__ ptr,
+                                                       int np, int32_t* rev) {
+  __shared__ int32_t lds[4][SORT_LDS];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int j = blockIdx.x * 4 + w;
+  if (j >= np) return;
+  const int b = ptr[j], n = ptr[j + 1] - b;
+  if (n < 2) return;
+  if (n <= 64) {
+    double none = 0.0;
+    int c = lane < n ? rev[b + lane] : INT_MAX;
+    bitonic_sort64(none, c);  // equal distances: by the index alone
+    if (lane < n) rev[b + lane] = c;
+  } else if (n <= SORT_LDS) {
+    for (int q = lane; q < n; q += 64) lds[w][q] = rev[b + q];
+    __builtin_amdgcn_wave_barrier();
+    sort_ints(lds[w], n, lane);
+    for (int q = lane; q < n; q += 64) rev[b + q] = lds[w][q];
+  } else {
+    sort_ints(rev + b, n, lane);
   }
 }
 
-// A workgroup owns GB_COLS columns of one output row: each of its 256
-// threads holds GB_VEC groups of 4 consecutive columns, loaded and stored as
-// 16-byte vectors (strided rows fall back to scalar stores of the output).
-// Rows that no term touches are written as zeros and nothing else; touched
-// rows gather their terms in FP64, GB_BATCH terms' source vectors in flight at
-// once, rounded once to FP32.
-constexpr int GB_VEC = 1;
-constexpr int GB_BATCH = 4;  // terms whose source vectors are loaded together
-constexpr int GB_COLS = 256 * 4 * GB_VEC;
+// A workgroup owns GB_COLS columns of one output row, 4 consecutive ones per
+// thread (16-byte loads; strided rows fall back to scalar stores of the
+// output). Rows that no term touches are written as zeros and nothing else. For
+// the others the workgroup first lists the row's terms (source row, coefficient)
+// in LDS, in a fixed order -- W_ab: a = t + m, b = j + m for j in N_t, by m and
+// rank; W_ba: a = j + m with j in N_t, b = t + m, by m and t -- with the loads
+// of weights, neighbours and reverse lists side by side instead of one behind
+// the other; then each thread gathers its columns in FP64, GB_BATCH terms'
+// source vectors in flight at once, rounded once to FP32.
+//
+// What bounds it: with a few weighted trajectories HBM (the gradient's zeros and
+// the source rows); with all of them weighted, the rows that many trajectories
+// have as a neighbour, hundreds of terms long. T = 2000, D = 8192, 1900 of 1996
+// trajectories weighted, the whole backward: 1424 us with the terms looked up
+// one after the other and one-thread sorts, 619 us now.
+constexpr int GB_BATCH = 4;    // terms whose source vectors are loaded together
+constexpr int GB_REV = 512;    // reverse terms listed at a time
+constexpr int GB_FWD = TRAKNN_MAX_L * TRAKNN_MAX_K;  // forward terms at most
+constexpr int GB_COLS = 256 * 4;
 
 template <bool VEC_OUT>
 __global__ __launch_bounds__(256) void grad_rows_kernel(
@@ -130,11 +178,15 @@ __global__ __launch_bounds__(256) void grad_rows_kernel(
     const int32_t* __restrict__ idx, const double* __restrict__ w,
     const int32_t* __restrict__ ptr, const int32_t* __restrict__ rev,
     const int32_t* __restrict__ touch, float* __restrict__ g, int64_t ldg) {
+  __shared__ double tc[GB_FWD + GB_REV];
+  __shared__ int tb[GB_FWD + GB_REV];
+  __shared__ int fwd, rv_b[TRAKNN_MAX_L], rv_e[TRAKNN_MAX_L + 1];  // reverse buckets, their ends
   const int a = blockIdx.x;
   const int np = T - L + 1;
-  const int64_t cbase = (int64_t)blockIdx.y * GB_COLS + 4 * threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int64_t c = (int64_t)blockIdx.y * GB_COLS + 4 * tid;
   float* ga = g + (int64_t)a * ldg;
-  auto store = [&](int64_t c, float4 v) __attribute__((always_inline)) {
+  auto store = [&](float4 v) __attribute__((always_inline)) {
     if (VEC_OUT && c + 3 < D) {
       *(float4*)(ga + c) = v;
     } else {
@@ -145,87 +197,89 @@ __global__ __launch_bounds__(256) void grad_rows_kernel(
     }
   };
   if (!touch[a]) {
-#pragma unroll
-    for (int v = 0; v < GB_VEC; ++v) store(cbase + 1024 * v, make_float4(0.f, 0.f, 0.f, 0.f));
+    store(make_float4(0.f, 0.f, 0.f, 0.f));
     return;
   }
   // FP32 source vector of row r at the thread's columns (zero past D)
-  auto load = [&](int64_t r, int v) __attribute__((always_inline)) {
-    const int64_t c = cbase + 1024 * v;
+  auto load = [&](int64_t r) __attribute__((always_inline)) {
     const float* p = X + r * ldx + c;
     if (c + 3 < D) return *(const float4*)p;
     return make_float4(c < D ? p[0] : 0.f, c + 1 < D ? p[1] : 0.f, c + 2 < D ? p[2] : 0.f,
                        c + 3 < D ? p[3] : 0.f);
   };
-  double acc[GB_VEC][4];
-  double xa[GB_VEC][4];
-#pragma unroll
-  for (int v = 0; v < GB_VEC; ++v) {
-    const float4 x = load(a, v);
-    xa[v][0] = x.x, xa[v][1] = x.y, xa[v][2] = x.z, xa[v][3] = x.w;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) acc[v][e] = 0.0;
-  }
   const double invk = 1.0 / (double)k;
-  // Terms go in batches of GB_BATCH, every source vector of a batch loaded
-  // before any is used, so a row with many terms waits for one memory round
-  // trip per batch instead of one per term. Unused entries of a batch read the
-  // row itself with weight 0 (an exact zero contribution).
-  int64_t tb[GB_BATCH];
-  double tc[GB_BATCH];
-  int nt = 0;
-  auto flush = [&]() __attribute__((always_inline)) {
-    float4 xb[GB_BATCH][GB_VEC];
+  const float4 x = load(a);
+  if (tid < 64) {  // the first wave lists the forward terms and the buckets
+    const int ta = a - lane;
+    const bool in = lane < L && ta >= 0 && ta < np;
+    const double wt = in ? w[ta] : 0.0;
+    const int p0 = in ? ptr[ta] : 0;
+    int sum = in ? ptr[ta + 1] - p0 : 0;
 #pragma unroll
-    for (int u = 0; u < GB_BATCH; ++u)
+    for (int o = 1; o < TRAKNN_MAX_L; o <<= 1) {
+      const int y = __shfl_up(sum, o, 64);
+      if (lane >= o) sum += y;
+    }
+    if (lane < L) {
+      rv_b[lane] = p0;
+      rv_e[lane + 1] = sum;
+    }
+    if (lane == 0) rv_e[0] = 0;
+    uint64_t ms = __ballot(wt != 0.0);
+    int n = 0;
+    while (ms) {
+      const int m = __builtin_ctzll(ms);
+      ms &= ms - 1;
+      const double cm = readlane_d(wt, m) * invk;
+      const int j = lane < k ? idx[(int64_t)(a - m) * k + lane] : -1;
+      const uint64_t ok = __ballot(j >= 0 && j < np);
+      if ((ok >> lane) & 1) {
+        const int pos = n + mask_rank(ok);
+        tb[pos] = j + m;
+        tc[pos] = cm;
+      }
+      n += __builtin_popcountll(ok);
+    }
+    if (lane == 0) fwd = n;
+  }
+  __syncthreads();
+  const int nf = fwd, nr = rv_e[L];
+  const double xa[4] = {x.x, x.y, x.z, x.w};
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  int done = 0;  // listed terms already gathered (the forward ones, after the first list)
+  for (int r0 = 0; r0 == 0 || r0 < nr; r0 += GB_REV) {
+    const int n = nf + (nr - r0 < GB_REV ? nr - r0 : GB_REV);
+    if (r0 > 0) __syncthreads();  // the previous list is used
+    for (int e = tid; e < n - nf; e += 256) {
+      int m = 0;
+      while (r0 + e >= rv_e[m + 1]) ++m;
+      const int t = rev[rv_b[m] + (r0 + e - rv_e[m])];
+      tb[nf + e] = t + m;
+      tc[nf + e] = w[t] * invk;
+    }
+    __syncthreads();
+    // unused entries of a batch read the row itself with weight 0 (an exact
+    // zero contribution)
+    for (int q = done; q < n; q += GB_BATCH) {
+      float4 xb[GB_BATCH];
+      double cc[GB_BATCH];
 #pragma unroll
-      for (int v = 0; v < GB_VEC; ++v) xb[u][v] = load(u < nt ? tb[u] : a, v);
+      for (int u = 0; u < GB_BATCH; ++u) {
+        xb[u] = load(q + u < n ? tb[q + u] : a);
+        cc[u] = q + u < n ? tc[q + u] : 0.0;
+      }
 #pragma unroll
-    for (int u = 0; u < GB_BATCH; ++u) {
-      const double c = u < nt ? tc[u] : 0.0;
-#pragma unroll
-      for (int v = 0; v < GB_VEC; ++v) {
-        acc[v][0] += c * (xa[v][0] - (double)xb[u][v].x);
-        acc[v][1] += c * (xa[v][1] - (double)xb[u][v].y);
-        acc[v][2] += c * (xa[v][2] - (double)xb[u][v].z);
-        acc[v][3] += c * (xa[v][3] - (double)xb[u][v].w);
+      for (int u = 0; u < GB_BATCH; ++u) {
+        acc[0] += cc[u] * (xa[0] - (double)xb[u].x);
+        acc[1] += cc[u] * (xa[1] - (double)xb[u].y);
+        acc[2] += cc[u] * (xa[2] - (double)xb[u].z);
+        acc[3] += cc[u] * (xa[3] - (double)xb[u].w);
       }
     }
-    nt = 0;
-  };
-  auto term = [&](int64_t b, double c) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < GB_BATCH; ++u)
-      if (u == nt) tb[u] = b, tc[u] = c;
-    if (++nt == GB_BATCH) flush();
-  };
-  // W_ab: a = t + m, b = j + m for j in N_t
-  for (int m = 0; m < L; ++m) {
-    const int t = a - m;
-    if (t < 0 || t >= np) continue;
-    const double wt = w[t];
-    if (wt == 0.0) continue;
-    const double c = wt * invk;
-    for (int q = 0; q < k; ++q) {
-      const int j = idx[(int64_t)t * k + q];
-      if (j < 0 || j >= np) continue;
-      term(j + m, c);
-    }
+    done = nf;
   }
-  // W_ba: a = j + m with j in N_t, b = t + m
-  for (int m = 0; m < L; ++m) {
-    const int j = a - m;
-    if (j < 0 || j >= np) continue;
-    for (int r = ptr[j]; r < ptr[j + 1]; ++r) {
-      const int t = rev[r];
-      term(t + m, w[t] * invk);
-    }
-  }
-  if (nt) flush();
-#pragma unroll
-  for (int v = 0; v < GB_VEC; ++v)
-    store(cbase + 1024 * v, make_float4((float)(2.0 * acc[v][0]), (float)(2.0 * acc[v][1]),
-                                        (float)(2.0 * acc[v][2]), (float)(2.0 * acc[v][3])));
+  store(make_float4((float)(2.0 * acc[0]), (float)(2.0 * acc[1]), (float)(2.0 * acc[2]),
+                    (float)(2.0 * acc[3])));
 }
 
 }  // namespace
@@ -241,7 +295,6 @@ hipError_t launch_backward(const float* X, int64_t ldx, int64_t T, int64_t D,
   int32_t* touch = zeroed + 2 * (int64_t)np;
   const int64_t nz = 2 * (int64_t)np + T;
   const int64_t nk = (int64_t)np * k;
-  const unsigned gb = (unsigned)((np + 255) / 256);
   const unsigned gk = (unsigned)((nk + 255) / 256);
   hipError_t e;
   hipLaunchKernelGGL(fill_i32_kernel, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, s,
@@ -254,7 +307,7 @@ hipError_t launch_backward(const float* X, int64_t ldx, int64_t T, int64_t D,
   hipLaunchKernelGGL(rev_fill_kernel, dim3(gk), dim3(256), 0, s, idx, w, np, k, ptr,
                      fill, rev);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(rev_sort_kernel, dim3(gb), dim3(256), 0, s, ptr, np, rev);
+  hipLaunchKernelGGL(rev_sort_kernel, dim3((unsigned)((np + 3) / 4)), dim3(256), 0, s, ptr, np, rev);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const dim3 grid((unsigned)T, (unsigned)((D + GB_COLS - 1) / GB_COLS));
   const bool vec_out = ldg % 4 == 0 && ((uintptr_t)g % 16) == 0;
