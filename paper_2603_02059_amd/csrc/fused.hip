@@ -22,16 +22,13 @@ namespace {
 
 constexpr int F64_TILE = FUSED_F64_TILE;   // snapshot rows and columns of a tile
 constexpr int F64_THREADS = 512;
-constexpr int F64_ROWS = F64_TILE / (F64_THREADS / 64);  // Gram rows per wave
 constexpr int F64_KC = 16;                 // cells per K chunk staged in LDS
 constexpr int F64_LD = F64_TILE + 1;       // pitch of the staged distance tile (odd)
-constexpr int F64_APITCH = F64_KC + 1;     // pitch of the A panel, doubles
-constexpr int F64_BPITCH = F64_TILE + 2;   // pitch of the transposed B panel, doubles
-constexpr int F64_PANEL_BYTES = (F64_TILE * F64_APITCH + F64_KC * F64_BPITCH) * 8;
+constexpr int F64_PITCH = F64_TILE + 2;    // pitch of a transposed panel, doubles (16-byte rows)
+constexpr int F64_PANEL_BYTES = 2 * F64_KC * F64_PITCH * 8;
 constexpr int F64_VAL_BYTES = F64_TILE * F64_LD * 4;
 constexpr int F64_UNION_BYTES = F64_PANEL_BYTES > F64_VAL_BYTES ? F64_PANEL_BYTES : F64_VAL_BYTES;
-static_assert(F64_TILE == 128 && F64_ROWS == 16,
-              "the Gram mapping gives each wave 16 rows and each lane 2 columns");
+static_assert(F64_TILE == 128 && F64_THREADS == 512, "eight waves of 32 x 64 entries");
 
 // Eq. 4 in FP64 from the two squared norms and the inner product: one rounding.
 __device__ __forceinline__ double f64_dist(double ni, double nj, double g) {
@@ -43,11 +40,13 @@ __device__ __forceinline__ double centred(const float* X, int64_t ldx, int T, in
   return (r < T && p < D) ? (double)X[r * ldx + p] - mu[p] : 0.0;
 }
 
-template <bool ESTABLISH>
-__global__ __launch_bounds__(F64_THREADS) void fused_f64_kernel(
+// ESTABLISH: the first round; SCAN: a later one by scan_part instead of
+// side_topk.
+template <bool ESTABLISH, bool SCAN>
+__global__ __launch_bounds__(F64_THREADS, 4) void fused_f64_kernel(
     const float* __restrict__ X, int64_t ldx, int D, const double* __restrict__ mu,
     FusedGeom g, const double* __restrict__ bound, FusedSlots out) {
-  __shared__ __attribute__((aligned(16))) char un[F64_UNION_BYTES];
+  __shared__ __attribute__((aligned(16))) char un[F64_UNION_BYTES + 8 * SCAN_PAD];
   __shared__ double nrm[2][F64_TILE];  // squared norms of the A and B rows
   __shared__ double est_d[F64_THREADS / 64][64];  // each wave's first-round scratch
   __shared__ int est_i[F64_THREADS / 64][64];
@@ -55,66 +54,110 @@ __global__ __launch_bounds__(F64_THREADS) void fused_f64_kernel(
   if (!fused_band_tile(blockIdx.x, g, I, J)) return;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int64_t i0 = (int64_t)I * g.B, j0 = (int64_t)J * g.B;
-  double* Ap = (double*)un;                    // [F64_TILE][F64_APITCH]
-  double* Bt = Ap + F64_TILE * F64_APITCH;     // [F64_KC][F64_BPITCH]
+  double* At = (double*)un;                // [F64_KC][F64_PITCH], transposed
+  double* Bt = At + F64_KC * F64_PITCH;    // [F64_KC][F64_PITCH]
 
-  // Gram of the tile: wave w owns the F64_ROWS rows from F64_ROWS w on (read
-  // as broadcasts), each lane the columns lane and lane + 64.
-  double acc[F64_ROWS][2];
+  // Gram of the tile: wave w owns 32 rows and 64 columns (a 4 x 2 grid), lane
+  // (lr, lc) of 8 x 8 the rows 2 lr, 2 lr + 1 of each 16 and the columns 2 lc,
+  // 2 lc + 1 of each 16: six 16-byte reads for 32 FMAs. (A wave of 16 rows, read
+  // as broadcasts, by 128 columns took 18 reads of 8 bytes for as many: the LDS
+  // then bound the product. T = 27394: 1.59 -> 1.43 ms a call at D = 13, k = 40,
+  // 2.22 -> 1.70 at D = 33, k = 10; the second register bound keeps two
+  // workgroups a CU, one took 2.04 and 2.42.)
+  const int wr = 32 * (w >> 1), wc = 64 * (w & 1);
+  const int lr = lane >> 3, lc = lane & 7;
+  double acc[4][8];
 #pragma unroll
-  for (int r = 0; r < F64_ROWS; ++r) acc[r][0] = acc[r][1] = 0.0;
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int q = 0; q < 8; ++q) acc[r][q] = 0.0;
   double nacc = 0.0;  // thread t < 128: A row t, 128 <= t < 256: B row t - 128
+  constexpr int PER = F64_TILE * F64_KC / F64_THREADS;  // cells a thread stages per panel
   for (int k0 = 0; k0 < D; k0 += F64_KC) {
     __syncthreads();  // previous chunk fully read
-    for (int e = tid; e < F64_TILE * F64_KC; e += F64_THREADS) {
-      const int r = e / F64_KC, c = e % F64_KC;
-      Ap[r * F64_APITCH + c] = centred(X, ldx, g.T, D, mu, i0 + r, k0 + c);
-      Bt[c * F64_BPITCH + r] = centred(X, ldx, g.T, D, mu, j0 + r, k0 + c);
+    double va[PER], vb[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int e = tid + u * F64_THREADS, r = e / F64_KC, c = e % F64_KC;
+      va[u] = centred(X, ldx, g.T, D, mu, i0 + r, k0 + c);
+      vb[u] = centred(X, ldx, g.T, D, mu, j0 + r, k0 + c);
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int e = tid + u * F64_THREADS, r = e / F64_KC, c = e % F64_KC;
+      At[c * F64_PITCH + r] = va[u];
+      Bt[c * F64_PITCH + r] = vb[u];
     }
     __syncthreads();
+    const int kc = D - k0 < F64_KC ? D - k0 : F64_KC;
     if (tid < 2 * F64_TILE) {
-      const bool a_side = tid < F64_TILE;
-      const int r = a_side ? tid : tid - F64_TILE;
-#pragma unroll
-      for (int c = 0; c < F64_KC; ++c) {
-        const double x = a_side ? Ap[r * F64_APITCH + c] : Bt[c * F64_BPITCH + r];
-        nacc = __builtin_fma(x, x, nacc);
-      }
+      const double* P = tid < F64_TILE ? At + tid : Bt + tid - F64_TILE;
+      for (int c = 0; c < kc; ++c) nacc = __builtin_fma(P[c * F64_PITCH], P[c * F64_PITCH], nacc);
     }
 #pragma unroll 1
-    for (int c = 0; c < F64_KC; ++c) {
-      const double b0 = Bt[c * F64_BPITCH + lane];
-      const double b1 = Bt[c * F64_BPITCH + lane + 64];
+    for (int c = 0; c < kc; ++c) {
+      double2 a[2], b[4];
 #pragma unroll
-      for (int r = 0; r < F64_ROWS; ++r) {
-        const double a = Ap[(F64_ROWS * w + r) * F64_APITCH + c];
-        acc[r][0] = __builtin_fma(a, b0, acc[r][0]);
-        acc[r][1] = __builtin_fma(a, b1, acc[r][1]);
-      }
+      for (int r = 0; r < 2; ++r) a[r] = *(const double2*)(At + c * F64_PITCH + wr + 16 * r + 2 * lr);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) b[q] = *(const double2*)(Bt + c * F64_PITCH + wc + 16 * q + 2 * lc);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+          acc[r][q] = __builtin_fma(r & 1 ? a[r >> 1].y : a[r >> 1].x,
+                                    q & 1 ? b[q >> 1].y : b[q >> 1].x, acc[r][q]);
     }
   }
   if (tid < 2 * F64_TILE) nrm[tid >> 7][tid & (F64_TILE - 1)] = nacc;
   __syncthreads();  // panels read, norms written
-  float* V = (float*)un;  // [F64_TILE][F64_LD] snapshot distances of the tile
+  float* V = (float*)un + SCAN_PAD;  // [F64_TILE][F64_LD] snapshot distances of the tile
 #pragma unroll
-  for (int r = 0; r < F64_ROWS; ++r) {
-    const int a = F64_ROWS * w + r;
+  for (int r = 0; r < 4; ++r) {
+    const int a = wr + 16 * (r >> 1) + 2 * lr + (r & 1);
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int b = lane + 64 * h;
-      V[a * F64_LD + b] = clamp_distance((float)f64_dist(nrm[0][a], nrm[1][b], acc[r][h]));
+    for (int q = 0; q < 8; ++q) {
+      const int b = wc + 16 * (q >> 1) + 2 * lc + (q & 1);
+      V[a * F64_LD + b] = clamp_distance((float)f64_dist(nrm[0][a], nrm[1][b], acc[r][q]));
     }
   }
-  __syncthreads();
-  // The row side (recipients = the tile's rows, slot J + 1) on the first half
-  // of the waves, the column side (recipients = its columns, slot I) on the
-  // second.
-  constexpr int NW = F64_THREADS / 64;
-  const int side = w / (NW / 2);
-  side_topk_len<F64_TILE / 64, ESTABLISH>(g.L, V, side ? 1 : F64_LD, side ? F64_LD : 1, g.B, g.B,
-                               (int)(side ? j0 : i0), (int)(side ? i0 : j0), side ? -1 : 1,
-                               side ? I : J + 1, g.np, w % (NW / 2), NW / 2, lane,
-                               bound, out, EstScratch{est_d[w], est_i[w]});
+  constexpr int NW = F64_THREADS / 64, NB = F64_TILE / 64;
+  const EstScratch sc{est_d[w], est_i[w]};
+  if constexpr (SCAN) {
+    // both sides' bounds and counters
+    __shared__ double rb[F64_TILE + SCAN_ROWS], cb[SCAN_COLS];
+    __shared__ int rc[F64_TILE], cc[F64_TILE];
+    scan_bounds(rb, rc, F64_TILE + SCAN_ROWS, g.B, (int)i0, g.np, bound, tid, F64_THREADS);
+    scan_bounds(cb + SCAN_ROWS, cc, SCAN_COLS - SCAN_ROWS, g.B, (int)j0, g.np, bound, tid, F64_THREADS);
+    if (tid < SCAN_ROWS) cb[tid] = -1.0;
+    __syncthreads();
+    with_length(g.L, [&](auto lc) __attribute__((always_inline)) {
+      constexpr int L = decltype(lc)::value;
+      scan_part<L>(V, F64_LD, F64_TILE, g.B, g.B, (int)i0, (int)j0, J + 1, I, out,
+                   ScanLds{rb, cb, rc, cc}, w, NW, lane);
+      __syncthreads();
+      bool over = scan_counts(rc, g.B, (int)i0, g.np, J + 1, out, tid, F64_THREADS);
+      over |= scan_counts(cc, g.B, (int)j0, g.np, I, out, tid, F64_THREADS);
+      // an overflowed slot is written again: its first writes have to be done
+      __builtin_amdgcn_s_waitcnt(0);
+      if (__syncthreads_or(over)) {
+        filter_overflow<L, NB>(V, F64_LD, 1, g.B, g.B, (int)i0, (int)j0, J + 1, g.np, rc, w, NW,
+                               lane, bound, out, sc);
+        filter_overflow<L, NB>(V, 1, F64_LD, g.B, g.B, (int)j0, (int)i0, I, g.np, cc, w, NW, lane,
+                               bound, out, sc);
+      }
+    });
+  } else {
+    __syncthreads();
+    // The row side (recipients = the tile's rows, slot J + 1) on the first half
+    // of the waves, the column side (recipients = its columns, slot I) on the
+    // second.
+    const int side = w / (NW / 2);
+    side_topk_len<NB, ESTABLISH>(g.L, V, side ? 1 : F64_LD, side ? F64_LD : 1, g.B, g.B,
+                                 (int)(side ? j0 : i0), (int)(side ? i0 : j0), side ? -1 : 1,
+                                 side ? I : J + 1, g.np, w % (NW / 2), NW / 2, lane, bound, out,
+                                 sc);
+  }
 }
 
 // One wave per row: the k nearest over some of the row's slots, starting
@@ -229,12 +272,13 @@ hipError_t launch_fused_f64(const float* X, int64_t ldx, int D, const double* mu
                             const FusedSlots& out, hipStream_t s) {
   const int64_t ntiles = fused_band_tiles(g);
   if (ntiles <= 0) return hipSuccess;
-  if (establish)
-    hipLaunchKernelGGL(fused_f64_kernel<true>, dim3((unsigned)ntiles), dim3(F64_THREADS), 0, s,
-                       X, ldx, D, mu, g, bound, out);
-  else
-    hipLaunchKernelGGL(fused_f64_kernel<false>, dim3((unsigned)ntiles), dim3(F64_THREADS), 0, s,
-                       X, ldx, D, mu, g, bound, out);
+#define TRAKNN_F64(E, C)                                                                        \
+  hipLaunchKernelGGL((fused_f64_kernel<E, C>), dim3((unsigned)ntiles), dim3(F64_THREADS), 0, s, \
+                     X, ldx, D, mu, g, bound, out)
+  if (establish) TRAKNN_F64(true, false);
+  else if (out.k >= SCAN_MIN_K) TRAKNN_F64(false, true);
+  else TRAKNN_F64(false, false);
+#undef TRAKNN_F64
   return hipGetLastError();
 }
 

@@ -29,6 +29,8 @@
 //    or more blocks from the diagonal, so no pair is in the exclusion zone.
 #pragma once
 
+#include <type_traits>
+
 #include "internal.h"
 #include "topk_wave.h"
 
@@ -344,6 +346,166 @@ __device__ __forceinline__ int recipient_establish(const float* V, int sp, int s
   return total < k ? total : k;
 }
 
+// The filter rounds' scan of a staged part, for both sides at once. Lane q of a
+// wave follows the diagonal that starts at column b0 = 64 c + q - 3 of row r0,
+// over SCAN_ROWS = 4 rows: 4 + L - 1 staged values give the lane's four
+// trajectory distances (direct L-term sums in increasing m, as the matrix
+// mode's windows start), each compared with its row's bound and with its
+// column's. A candidate within a bound takes a place in the recipient's slot by
+// an LDS counter, unsorted; a recipient with more than k of them is left to
+// filter_overflow. So a pair is read and summed once for both sides, and what a
+// recipient costs by itself is one counter, where side_topk reads every pair L
+// times for either side with a wave per recipient. Calls in FP64 at T = 27394,
+// L = 5, side_topk -> scan_part: D = 13, k = 40 1.78 -> 1.59 ms; D = 33, k = 10
+// 2.34 -> 2.22 ms. With few places per slot (k = 3: 0.43 -> 0.45 ms at T =
+// 12000) the recipients that overflow take the gain back, hence SCAN_MIN_K. The
+// MFMA consumer keeps side_topk: it would have to stage the columns that
+// overflow (L = 12, k = 10, T = 12000 in FP16: 0.79 -> 0.91 ms).
+constexpr int SCAN_MIN_K = 8;
+constexpr int SCAN_ROWS = 4;
+constexpr int SCAN_PAD = SCAN_ROWS;  // floats a staged part has to itself either side
+constexpr int SCAN_COLS = 64 * ((FUSED_F64_TILE + SCAN_ROWS - 1 + 63) / 64) + 2 * SCAN_ROWS;
+// Bounds and counters of a part's recipients: rows a (rb[a], rc[a], up to the
+// next multiple of SCAN_ROWS) and columns b (cb[b + SCAN_ROWS], cc[b]). A bound
+// of -1 marks a row or column that does not exist.
+struct ScanLds {
+  double* rb;
+  double* cb;
+  int* rc;
+  int* cc;
+};
+// V: [nrow][ld] staged distances of P row and Q column trajectories, the first
+// of them p0 and q0.
+template <int L>
+__device__ __forceinline__ void scan_part(const float* V, int ld, int nrow, int P, int Q, int p0,
+                                          int q0, int rslot, int cslot, const FusedSlots& out,
+                                          const ScanLds& sl, int wave, int nw, int lane) {
+  constexpr int R = SCAN_ROWS, M = R + L - 1;
+  const int nch = (Q + R - 1 + 63) / 64, nblk = (P + R - 1) / R;
+  const int k = out.k;
+  int blk = wave / nch, c = wave % nch;
+  const int dblk = nw / nch, dc = nw % nch;
+  float x[M];
+  auto read = [&](int blk, int c) __attribute__((always_inline)) {
+    const int b0 = 64 * c + lane - (R - 1);
+    const int bc = b0 < Q - 1 ? b0 : Q - 1;  // lanes past the last column: a valid address
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      const int row = R * blk + m < nrow ? R * blk + m : nrow - 1;
+      x[m] = V[row * ld + bc + m];
+    }
+  };
+  while (blk < nblk) {
+    const int r0 = R * blk;
+    const int b0 = 64 * c + lane - (R - 1);
+    read(blk, c);
+    double v[M];
+#pragma unroll
+    for (int m = 0; m < M; ++m) v[m] = m < R - 1 && b0 + m < 0 ? 0.0 : (double)x[m];
+    blk += dblk;
+    c += dc;
+    if (c >= nch) {
+      c -= nch;
+      ++blk;
+    }
+    double D[R];
+    uint64_t mr[R], mc[R];
+    uint64_t any = 0;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      D[j] = v[j];
+#pragma unroll
+      for (int m = 1; m < L; ++m) D[j] += v[j + m];
+      const double cb = sl.cb[b0 + j + R], rb = sl.rb[r0 + j];
+      const uint64_t there = __ballot(cb >= 0.0) & __ballot(rb >= 0.0);
+      mr[j] = __ballot(D[j] <= rb) & there;
+      mc[j] = __ballot(D[j] <= cb) & there;
+      any |= mr[j] | mc[j];
+    }
+    if (any) {
+      // every counter at once: lane j row j's, each lane its columns'
+      int n = 0;
+#pragma unroll
+      for (int j = 0; j < R; ++j)
+        n = lane_select((uint64_t)1 << j, (int)__builtin_popcountll(mr[j]), n);
+      int at = 0, pos[R];
+      if (n) at = __hip_atomic_fetch_add(&sl.rc[r0 + lane], n, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        pos[j] = k;
+        if ((mc[j] >> lane) & 1)
+          pos[j] = __hip_atomic_fetch_add(&sl.cc[b0 + j], 1, __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        const int a = r0 + j, b = b0 + j;
+        if (mr[j]) {
+          const int pr = __builtin_amdgcn_readlane(at, j) + mask_rank(mr[j]);
+          if (((mr[j] >> lane) & 1) && pr < k) {
+            const int64_t o = ((int64_t)(p0 + a) * out.nslot + rslot) * k + pr;
+            out.d[o] = D[j];
+            out.i[o] = q0 + b;
+          }
+        }
+        if (pos[j] < k) {
+          const int64_t o = ((int64_t)(q0 + b) * out.nslot + cslot) * k + pos[j];
+          out.d[o] = D[j];
+          out.i[o] = p0 + a;
+        }
+      }
+    }
+  }
+}
+
+// Bounds of recipients p0 .. p0 + P - 1 into b (n entries, -1 past the last) and
+// their counters cleared.
+__device__ __forceinline__ void scan_bounds(double* b, int* cnt, int n, int P, int p0, int np,
+                                            const double* bound, int tid, int nthreads) {
+  for (int q = tid; q < n; q += nthreads) {
+    const bool there = q < P && p0 + q < np;
+    b[q] = there ? bound[p0 + q] : -1.0;
+    if (q < P) cnt[q] = 0;
+  }
+}
+
+// The slots' counts of recipients p0 .. p0 + P - 1; returns whether one of them
+// (of the thread's) has more candidates than its slot holds.
+__device__ __forceinline__ bool scan_counts(const int* cnt, int P, int p0, int np, int slot,
+                                            const FusedSlots& out, int tid, int nthreads) {
+  bool over = false;
+  for (int q = tid; q < P; q += nthreads) {
+    if (p0 + q >= np) continue;
+    const int n = cnt[q];
+    over |= n > out.k;
+    out.cnt[(int64_t)(p0 + q) * out.nslot + slot] = n < out.k ? n : out.k;
+  }
+  return over;
+}
+
+// The recipients of one side whose candidates overflowed their slots (cnt[s] >
+// k, s = s0 .. s0 + P - 1 staged as 0 .. P - 1): the k nearest, by
+// recipient_topk.
+template <int L, int NB>
+__device__ __forceinline__ void filter_overflow(const float* V, int sp, int sq, int Q, int P,
+                                                int p0, int q0, int slot, int np, const int* cnt,
+                                                int wave, int nw, int lane, const double* bound,
+                                                const FusedSlots& out, const EstScratch& sc) {
+  uint64_t rng[NB];
+  batch_masks<NB>(Q, q0, np, -1, 1, L, lane, rng);
+#pragma unroll 1
+  for (int s = wave; s < P; s += nw) {
+    if (p0 + s >= np || __builtin_amdgcn_readfirstlane(cnt[s]) <= out.k) continue;
+    const double b = bound[p0 + s];
+    double ed;
+    int ei;
+    const int n = recipient_topk<L, NB, true>(V, sp, sq, Q, s, q0, rng, out.k, b,
+                                              prefilter_bound(b), lane, sc, ed, ei);
+    slot_write(out, p0 + s, slot, n, ed, ei, lane);
+  }
+}
+
 // One side of a staged part: wave w of nw keeps recipients w, w + nw, ... of
 // 0 .. P - 1 and writes their slots. ESTABLISH (the first round): each
 // recipient's exact k nearest in the tile (recipient_establish, using the
@@ -403,6 +565,15 @@ __device__ __forceinline__ void side_topk_len(int L, const float* V, int sp, int
     else
       side_topk_len<NB, ESTABLISH, LC + 1>(L, V, sp, sq, Q, P, p0, q0, sign, slot, np, wave, nw,
                                            lane, bound, out, sc);
+  }
+}
+
+// f(integral_constant<L>) for the run-time length L (1 .. TRAKNN_MAX_L).
+template <int LC = 1, typename F>
+__device__ __forceinline__ void with_length(int L, F f) {
+  if constexpr (LC <= TRAKNN_MAX_L) {
+    if (L == LC) f(std::integral_constant<int, LC>{});
+    else with_length<LC + 1>(L, f);
   }
 }
 
