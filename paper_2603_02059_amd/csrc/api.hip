@@ -296,14 +296,16 @@ int enqueue_knn(traknn_plan_s* plan, const float* X, int64_t ldx, void* workspac
   float* S = at<float>(workspace, L.S);
 
   if ((rc = record(plan, 0, s))) return rc;
-  if ((rc = fail_hip(launch_colstats(X, ldx, plan->T, plan->D, plan->tchunks,
-                                     mu_part, mu, s))))
+  const bool convert = c.precision != TRAKNN_FP64;
+  const bool reduce = !convert || plan->tchunks > INLINE_PARTS;
+  if ((rc = fail_hip(launch_colstats(X, ldx, plan->T, plan->D, plan->tchunks, reduce, mu_part, mu,
+                                     s))))
     return rc;
   if ((rc = record(plan, 1, s))) return rc;
-  if (c.precision != TRAKNN_FP64 &&
-      (rc = fail_hip(launch_centre_convert(X, ldx, plan->T, plan->D, plan->Tpad,
-                                           plan->Dpad, c.precision, mu, xc,
-                                           ncs, s))))
+  if (convert &&
+      (rc = fail_hip(launch_centre_convert(X, ldx, plan->T, plan->D, plan->Tpad, plan->Dpad,
+                                           c.precision, reduce ? 0 : plan->tchunks,
+                                           reduce ? mu : mu_part, xc, ncs, s))))
     return rc;
   if ((rc = record(plan, 2, s))) return rc;
   if (plan->fused) return enqueue_fused(plan, X, ldx, workspace, nbr_idx, nbr_dist, s);

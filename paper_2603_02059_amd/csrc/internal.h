@@ -127,13 +127,20 @@ struct traknn_plan_s {
 namespace traknn {
 
 // prep.hip
+// The per-cell shift: partial sums of tchunks blocks of samples, and unless
+// the centring is to add them itself (reduce false), their mean.
 hipError_t launch_colstats(const float* X, int64_t ldx, int64_t T, int64_t D,
-                           int tchunks, double* mu_part, double* mu,
+                           int tchunks, bool reduce, double* mu_part, double* mu,
                            hipStream_t s);
+// parts 0: mu is the shift; else it is that many blocks of partial sums.
 hipError_t launch_centre_convert(const float* X, int64_t ldx, int64_t T,
                                  int64_t D, int64_t Tpad, int64_t Dpad,
-                                 int precision, const double* mu, void* xc,
+                                 int precision, int parts, const double* mu, void* xc,
                                  float* ncs, hipStream_t s);
+// Up to this many blocks of partial sums are added by every wave of the
+// centring itself (32 KB of reads a wave at most), which saves a short series
+// the reduction's launch.
+constexpr int INLINE_PARTS = 4;
 // gram.hip
 hipError_t launch_gram(const void* xc, const float* ncs, int64_t T, int64_t Tpad,
                        int64_t Dpad, int precision, float* S, int64_t ldS, hipStream_t s);

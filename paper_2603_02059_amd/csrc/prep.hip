@@ -24,54 +24,42 @@ namespace traknn {
 namespace {
 
 // Partial column sums of the sampled rows (sample r is row r * stride) over
-// blocks of COLSTAT_ROWS samples: each thread sums 4 consecutive cells (one
-// 16-byte load per row, 1 KB per wave and row), eight rows in flight at a
-// time, in a fixed order.
+// blocks of COLSTAT_ROWS samples, one cell a thread (a wave reads 256 bytes of
+// a row), COLSUM_BATCH rows in flight at a time, in a fixed order. The sample is
+// at most 2048 rows, so latency bounds it on all but the widest grids: with
+// four cells a thread and eight rows in flight the 128 rows of a block took 16
+// round trips on a quarter of the waves (25 us for 1827 samples of 1961 cells,
+// 7 us now).
+constexpr int COLSUM_BATCH = 32;
 __global__ __launch_bounds__(256) void colsum_partial_kernel(
     const float* __restrict__ X, int64_t ldx, int64_t nsamp, int64_t stride, int64_t D,
     double* __restrict__ part) {
-  const int64_t c = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x);
+  const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t r0 = (int64_t)blockIdx.y * COLSTAT_ROWS;
   if (c >= D) return;
   const int64_t r1 = r0 + COLSTAT_ROWS < nsamp ? r0 + COLSTAT_ROWS : nsamp;
   const int64_t step = stride * ldx;  // floats between sampled rows
-  double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-  if (c + 4 <= D) {
-    const float* p = X + r0 * step + c;
-    int64_t r = r0;
-    for (; r + 8 <= r1; r += 8) {
-      float4 v[8];
+  const float* p = X + r0 * step + c;
+  double s = 0.0;
+  int64_t r = r0;
+  for (; r + COLSUM_BATCH <= r1; r += COLSUM_BATCH) {
+    float v[COLSUM_BATCH];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = *(const float4*)(p + u * step);
+    for (int u = 0; u < COLSUM_BATCH; ++u) v[u] = p[u * step];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        s0 += (double)v[u].x;
-        s1 += (double)v[u].y;
-        s2 += (double)v[u].z;
-        s3 += (double)v[u].w;
-      }
-      p += 8 * step;
-    }
-    for (; r < r1; ++r, p += step) {
-      const float4 v = *(const float4*)p;
-      s0 += (double)v.x;
-      s1 += (double)v.y;
-      s2 += (double)v.z;
-      s3 += (double)v.w;
-    }
-  } else {
-    for (int64_t r = r0; r < r1; ++r) {
-      const float* p = X + r * step + c;
-      s0 += (double)p[0];
-      if (c + 1 < D) s1 += (double)p[1];
-      if (c + 2 < D) s2 += (double)p[2];
-    }
+    for (int u = 0; u < COLSUM_BATCH; ++u) s += (double)v[u];
+    p += COLSUM_BATCH * step;
   }
-  double* out = part + (int64_t)blockIdx.y * D + c;
-  out[0] = s0;
-  if (c + 1 < D) out[1] = s1;
-  if (c + 2 < D) out[2] = s2;
-  if (c + 3 < D) out[3] = s3;
+  if (r < r1) {
+    const int n = (int)(r1 - r);
+    float v[COLSUM_BATCH];
+#pragma unroll
+    for (int u = 0; u < COLSUM_BATCH; ++u) v[u] = p[(u < n ? u : 0) * step];
+#pragma unroll
+    for (int u = 0; u < COLSUM_BATCH; ++u)
+      if (u < n) s += (double)v[u];
+  }
+  part[(int64_t)blockIdx.y * D + c] = s;
 }
 
 // Fixed-order reduction of the partial sums -> per-cell sample mean.
@@ -180,7 +168,7 @@ constexpr int CONV_BATCH = 4;
 template <int PREC>
 __global__ __launch_bounds__(256) void centre_convert_kernel(
     const float* __restrict__ X, int64_t ldx, int64_t T, int64_t D,
-    int64_t Tpad, int64_t Dpad, const double* __restrict__ mu,
+    int64_t Tpad, int64_t Dpad, const double* __restrict__ mu, int parts, double nsamp,
     char* __restrict__ xc, float* __restrict__ ncs, int nrows) {
   static_assert(GRAM_CHUNK == 64 * 8, "a wave covers one norm chunk");
   constexpr int LB = conv_bytes<PREC>();  // bytes a lane emits per row
@@ -199,8 +187,18 @@ __global__ __launch_bounds__(256) void centre_convert_kernel(
   const bool full = e0 + 8 <= D;
   const int64_t sl0 = ch * NSL, nsl = Dpad * LB / 8 / GRAM_ROW_BYTES;
   double m[8];
+  if (parts == 0) {
 #pragma unroll
-  for (int u = 0; u < 8; ++u) m[u] = e0 + u < D ? mu[e0 + u] : 0.0;
+    for (int u = 0; u < 8; ++u) m[u] = e0 + u < D ? mu[e0 + u] : 0.0;
+  } else {  // mu holds the partial sums: their reduction, as colsum_reduce_kernel's
+#pragma unroll
+    for (int u = 0; u < 8; ++u) m[u] = 0.0;
+    for (int q = 0; q < parts; ++q)
+#pragma unroll
+      for (int u = 0; u < 8; ++u) m[u] += e0 + u < D ? mu[q * D + e0 + u] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) m[u] /= nsamp;
+  }
   for (int64_t i0 = ib; i0 < ib + nrows && i0 < Tpad; i0 += CONV_BATCH) {
     float x[CONV_BATCH][8];
 #pragma unroll
@@ -254,15 +252,15 @@ __global__ __launch_bounds__(256) void centre_convert_kernel(
 }  // namespace
 
 hipError_t launch_colstats(const float* X, int64_t ldx, int64_t T, int64_t D,
-                           int tchunks, double* mu_part, double* mu,
+                           int tchunks, bool reduce, double* mu_part, double* mu,
                            hipStream_t s) {
   const int64_t stride = colstat_stride(T);
   const int64_t nsamp = (T + stride - 1) / stride;
-  dim3 g1((unsigned)((D + 1023) / 1024), (unsigned)tchunks);
+  dim3 g1((unsigned)((D + 255) / 256), (unsigned)tchunks);
   hipLaunchKernelGGL(colsum_partial_kernel, g1, dim3(256), 0, s, X, ldx, nsamp, stride, D,
                      mu_part);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || !reduce) return e;
   hipLaunchKernelGGL(colsum_reduce_kernel, dim3((unsigned)((D + 255) / 256)),
                      dim3(256), 0, s, mu_part, nsamp, D, tchunks, mu);
   return hipGetLastError();
@@ -270,8 +268,10 @@ hipError_t launch_colstats(const float* X, int64_t ldx, int64_t T, int64_t D,
 
 hipError_t launch_centre_convert(const float* X, int64_t ldx, int64_t T,
                                  int64_t D, int64_t Tpad, int64_t Dpad,
-                                 int precision, const double* mu, void* xc,
+                                 int precision, int parts, const double* mu, void* xc,
                                  float* ncs, hipStream_t s) {
+  const int64_t stride = colstat_stride(T);
+  const double nsamp = (double)((T + stride - 1) / stride);
   // Rows per wave: 16 (the chunk's means are read once for them), fewer while
   // that leaves less than CONV_WAVES waves (16 per CU), so that a short series
   // is one memory latency deep instead of four: 18 -> 9 us on 512 x 1024 fields.
@@ -282,7 +282,7 @@ hipError_t launch_centre_convert(const float* X, int64_t ldx, int64_t T,
   const dim3 g((unsigned)((nch * ((Tpad + nrows - 1) / nrows) + 3) / 4));
 #define TRAKNN_CONVERT(P)                                                                        \
   hipLaunchKernelGGL(centre_convert_kernel<P>, g, dim3(256), 0, s, X, ldx, T, D, Tpad, Dpad, mu, \
-                     (char*)xc, ncs, nrows)
+                     parts, nsamp, (char*)xc, ncs, nrows)
   if (precision == TRAKNN_FP32) TRAKNN_CONVERT(TRAKNN_FP32);
   else if (precision == TRAKNN_BF16X3) TRAKNN_CONVERT(TRAKNN_BF16X3);
   else TRAKNN_CONVERT(TRAKNN_FP16);
