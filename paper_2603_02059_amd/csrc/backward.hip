@@ -20,6 +20,8 @@
 namespace traknn {
 namespace {
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 __global__ __launch_bounds__(256) void fill_i32_kernel(int32_t* p, int64_t n,
                                                        int32_t v) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -106,7 +108,7 @@ __global__ __launch_bounds__(256) void rev_fill_kernel(
 // pairs an element with its mirror image), so that positions past the end act
 // as +inf. Buckets hold k entries on average, but a trajectory near the centre
 // of its data is a neighbour of hundreds: with one thread per bucket (insertion
-// sort) the longest of T = 1461, k = 10 took 205 us, this 6 us.
+// sort) the longest of T = 1461, k = 10 took 205 us, this 8 us.
 constexpr int SORT_LDS = 1024;
 __device__ __forceinline__ void sort_ints(int32_t* v, int n, int lane) {
   for (int size = 2; size < 2 * n; size <<= 1) {
@@ -163,10 +165,14 @@ __global__ __launch_bounds__(256) void rev_sort_kernel(const int32_t* __restrict
 // source vectors in flight at once, rounded once to FP32.
 //
 // What bounds it: with a few weighted trajectories HBM (the gradient's zeros and
-// the source rows); with all of them weighted, the rows that many trajectories
-// have as a neighbour, hundreds of terms long. T = 2000, D = 8192, 1900 of 1996
-// trajectories weighted, the whole backward: 1424 us with the terms looked up
-// one after the other and one-thread sorts, 619 us now.
+// the source rows). The gradient is written once and not read here, so its
+// stores are non-temporal: T = 10957, D = 8192 (359 MB), 100 trajectories
+// weighted, the whole backward: 148 -> 105 us. (One workgroup a row for the zero
+// rows instead of one per GB_COLS columns: 139 us.) With all of them weighted,
+// the rows that many trajectories have as a neighbour, hundreds of terms long:
+// T = 2000, D = 8192, 1900 of 1996 trajectories weighted, the whole backward:
+// 1424 us with the terms looked up one after the other and one-thread sorts,
+// 624 us now.
 constexpr int GB_BATCH = 4;    // terms whose source vectors are loaded together
 constexpr int GB_REV = 512;    // reverse terms listed at a time
 constexpr int GB_FWD = TRAKNN_MAX_L * TRAKNN_MAX_K;  // forward terms at most
@@ -188,7 +194,7 @@ __global__ __launch_bounds__(256) void grad_rows_kernel(
   float* ga = g + (int64_t)a * ldg;
   auto store = [&](float4 v) __attribute__((always_inline)) {
     if (VEC_OUT && c + 3 < D) {
-      *(float4*)(ga + c) = v;
+      __builtin_nontemporal_store(f32x4{v.x, v.y, v.z, v.w}, (f32x4*)(ga + c));
     } else {
       if (c < D) ga[c] = v.x;
       if (c + 1 < D) ga[c + 1] = v.y;
