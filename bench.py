@@ -4,7 +4,7 @@ Workload: T = 27394 daily fields (75 years) of a 64 x 128 grid (D = 8192),
 trajectory length L = 5, k = 10 neighbours, synthetic SLP-shaped fields (see
 paper_2603_02059_amd/synth.py). One step = one whole pass of the hot path on
 device-resident X: centring/conversion, symmetric Gram + distances, window
-recurrence + exclusion-zone top-k, merge, scores.
+recurrence + exclusion-zone top-k, scores.
 
 Metric: trajectory pairs per second, n'^2 / step time with n' = T - L + 1.
 The headline path is the split BF16x3 Gram; the plain FP32 and single-pass
@@ -189,7 +189,7 @@ def time_path(tk, torch, X, w, prec, steps, warmup, row_batch=0):
 
 def time_sweep(tk, torch, X, w, steps, warmup, L_max=10):
     """The all-lengths configuration: L = 1..L_max in one call on the full
-    workload, BF16x3 (one Gram, the window passes two lengths at a time)."""
+    workload, BF16x3 (one Gram, the window passes up to ten lengths at a time)."""
     p = tk.Plan(w.T, w.D, 1, L_max, w.k, "bf16x3")
     idx, dist = p.empty_outputs()
     scores = torch.empty((p.NL, p.np0), dtype=torch.float64, device=X.device)

@@ -134,14 +134,14 @@ extern "C" {
  *               plan places the pass starts on multiples of 8 so that the
  *               passes' partly idle last rounds of tiles cost least), and
  *               computes the rows t0 .. t1 + L_max - 2 of the matrix against
- *               the columns from t0 on, only the 256 x 256 tiles holding
+ *               the columns from t0 on, only the tiles of pairs holding
  *               entries above the diagonal, stored as rows and transposed.
  *               Its rows' later candidates come from the rows, and every
  *               later row's candidates among its trajectories from the
- *               transposed copy (the matrix is symmetric); both are merged
- *               into running lists, final for its rows when it ends. So the
+ *               transposed copy (the matrix is symmetric); both start
+ *               from running lists, final for its rows when it ends. So the
  *               Gram work is that of the whole-matrix mode plus about one
- *               diagonal tile per 256-row block-row of each pass, and the
+ *               diagonal tile per block-row of each pass, and the
  *               workspace holds (row_batch + L_max - 1) rows of the matrix
  *               plus T rows of row_batch + L_max - 1 entries. Each distance
  *               above the diagonal comes from the same operands in the same
@@ -312,9 +312,9 @@ const char* traknn_status_string(int status);
  * stages; traknn_stage_times then waits for the last event and returns the
  * elapsed milliseconds of each stage in launch order:
  *   0 centre statistics, 1 centre/convert/norms, 2 Gram + distance epilogue
- *   (in band mode: all passes, each Gram + window + merge),
- *   3 window recurrence + partial top-k, 4 top-k merge (both about 0 in band
- *   mode).
+ *   (in band mode: all passes, each Gram + windows),
+ *   3 window recurrence + top-k (about 0 in band mode), 4 about 0 (a merge
+ *   of partial lists; the window writes the final ones).
  *   enable   [in]  nonzero to record events from the next traknn_knn call on.
  *   ms       [out] host array of at least max_stages doubles.
  *   n_stages [out] number of stages written.
