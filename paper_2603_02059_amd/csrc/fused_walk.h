@@ -13,7 +13,8 @@
 // (candidate j) on the tile's ROW side and for row j (candidate i) on its
 // COLUMN side. The column side is the row side of the transposed tile, so one
 // routine serves both: the recipient axis p and the candidate axis q of the
-// staged values are addressed as V[p * sp + q * sq].
+// staged values are addressed as V[p * sp + q * sq]. scan_part instead walks the
+// tile's diagonals once for both sides (the FP64 tiles' later rounds).
 //
 // Every (recipient, tile side) writes the list of its candidates it keeps --
 // at most k -- to its own slot (FusedSlots), and a select kernel takes the k

@@ -152,7 +152,7 @@ def row_batch_for(T: int, D: int, L_min: int, L_max: int, k: int,
     """A row_batch whose workspace fits in max_bytes: 0 (the whole matrix, the
     faster mode) when that fits, else the largest multiple of 8 a bisection
     finds. Band mode's workspace grows with row_batch (both stored copies of
-    the band do), up to a wobble of the window's partial lists of a few MB.
+    the band do), up to a wobble of a few MB (a region kept in the layout, no longer used).
     Raises ValueError if even passes of 8 rows do not fit."""
     if workspace_bytes(T, D, L_min, L_max, k, precision, 0) <= max_bytes:
         return 0
