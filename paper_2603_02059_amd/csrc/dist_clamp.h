@@ -4,8 +4,10 @@
 // below zero for near-identical fields; such values become 0. A non-finite
 // value (NaN or -inf, from non-finite inputs or an FP16 overflow when
 // |x - mean| >= 65504) becomes +inf, so that a poisoned pair is never ranked
-// as a near neighbour: +inf and the NaN window sums it leads to never pass a
-// top-k bound. Plain C++, so the host tests compile it too.
+// as a near neighbour: the window and the fused select list no distance that is
+// +inf, and the NaN window sums it leads to pass no bound, so a row without k
+// finite candidates ends in index -1 and distance +inf. Plain C++, so the host
+// tests compile it too.
 #pragma once
 
 #if defined(__HIPCC__)

@@ -13,6 +13,8 @@
 // 2^-53 N, far below any tolerance. The distance is then rounded once to
 // FP32, as the distance matrix of the other modes stores it, and the tile
 // consumer (fused_walk.h) does the rest.
+#include <cfloat>
+
 #include "dist_clamp.h"
 #include "fused_walk.h"
 #include "internal.h"
@@ -236,7 +238,8 @@ __global__ __launch_bounds__(64 * SEL_WAVES) void select_kernel(
         }
         const double kd = readlane_d(ed, k - 1);
         const int ki = __builtin_amdgcn_readlane(ei, k - 1);
-        const bool pass = e < p1 && key_less(d, c, kd, ki);
+        // below +inf: not a lane past the entries, nor a distance that is +inf
+        const bool pass = (d <= DBL_MAX) & key_less(d, c, kd, ki);
         const uint64_t m = __ballot(pass);
         merge_batch(m, d, c, k, ed, ei, mrg_d[w], mrg_i[w], lane);
       }

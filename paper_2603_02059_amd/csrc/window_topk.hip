@@ -32,6 +32,7 @@
 // depend on the order in which the waves run, nor on how the lengths are
 // grouped into passes.
 #include <array>
+#include <cfloat>
 #include <climits>
 #include <type_traits>
 #include <utility>
@@ -121,6 +122,7 @@ __device__ __forceinline__ void dense_merge(const double* dump, int col, int k, 
     for (int u = 0; u < W1_WAVES; ++u) mn = __builtin_fmin(mn, dump[u * STEP + lane]);
     tau = readlane_d(sort_dist64(mn), k - 1);
   }
+  tau = __builtin_fmin(tau, DBL_MAX);  // +inf is not listed
   int total = 0;  // entries in the scratch
   auto absorb = [&]() __attribute__((always_inline)) {
     __builtin_amdgcn_wave_barrier();
@@ -408,8 +410,9 @@ __global__ __launch_bounds__(64 * W1_WAVES, 4) void window1_kernel(
         double ed;
         int ei;
         get(g, ed, ei);
-        const uint64_t m = __ballot(lane < n && key_less(d, ci, readlane_d(ed, k - 1),
-                                                         __builtin_amdgcn_readlane(ei, k - 1)));
+        // below +inf: not a lane past the entries, nor a distance that is +inf
+        const uint64_t m = __ballot((d <= DBL_MAX) & key_less(d, ci, readlane_d(ed, k - 1),
+                                                              __builtin_amdgcn_readlane(ei, k - 1)));
         if (!m) continue;
         merge_batch(m, d, ci, k, ed, ei, scr_d[w], scr_i[w], lane);
         put(g, ed, ei);
