@@ -185,6 +185,14 @@ __global__ __launch_bounds__(64 * W1_WAVES, 4) void window1_kernel(
   __shared__ __attribute__((aligned(16))) double bnd[G * R];
   __shared__ int cnt[W1_CNT][G * R];
   extern __shared__ __attribute__((aligned(16))) char lists[];  // G > 1: [G][R][k]
+  // An owner lowers a bound while other waves, already in the next round, read
+  // it: relaxed atomics, so that a read sees the old value or the new one.
+  auto bound_read = [&](int i) __attribute__((always_inline)) {
+    return __hip_atomic_load(&bnd[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+  auto bound_write = [&](int i, double v) __attribute__((always_inline)) {
+    __hip_atomic_store(&bnd[i], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
   double* const dump = (double*)pool;   // [W][R][64]
   double* const buf_d = (double*)pool;  // [2][G][R][CAP]
   int* const buf_i = (int*)(pool + 2 * BUF * 8);
@@ -271,7 +279,7 @@ __global__ __launch_bounds__(64 * W1_WAVES, 4) void window1_kernel(
       list_i[g * R * k] = ei;
     }
     const double kth = readlane_d(ed, k - 1);
-    if (lane == 0) bnd[g * R + w] = kth;
+    if (lane == 0) bound_write(g * R + w, kth);
   };
 #pragma unroll 1
   for (int g = 0; g < G; ++g) {
@@ -284,7 +292,7 @@ __global__ __launch_bounds__(64 * W1_WAVES, 4) void window1_kernel(
       ei = idx[o] < 0 ? INT_MAX : idx[o];
     }
     put(g, ed, ei);
-    if (!there && lane == 0) bnd[g * R + w] = -__builtin_huge_val();  // no such row: nothing passes
+    if (!there && lane == 0) bound_write(g * R + w, -__builtin_huge_val());  // no such row: nothing passes
   }
   for (int q = threadIdx.x; q < W1_CNT * G * R; q += 64 * W) (&cnt[0][0])[q] = 0;
   lds_barrier();
@@ -343,10 +351,10 @@ __global__ __launch_bounds__(64 * W1_WAVES, 4) void window1_kernel(
         // the rows' bounds: with one length from a lane each, which keeps the
         // registers of seven waves per SIMD; else the same in every lane, which
         // saves the lane reads
-        const double bl = bnd[g * R + (G == 1 ? (lane & (R - 1)) : 0)];
+        const double bl = G == 1 ? bound_read(lane & (R - 1)) : 0.0;
         double bound[R];
 #pragma unroll
-        for (int j = 0; j < R; ++j) bound[j] = G == 1 ? readlane_d(bl, j) : bnd[g * R + j];
+        for (int j = 0; j < R; ++j) bound[j] = G == 1 ? readlane_d(bl, j) : bound_read(g * R + j);
         double Dj[R];
         if constexpr (G == 1) {
 #pragma unroll
