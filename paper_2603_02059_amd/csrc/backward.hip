@@ -165,10 +165,10 @@ __global__ __launch_bounds__(256) void rev_sort_kernel(const int32_t* __restrict
 // source vectors in flight at once, rounded once to FP32.
 //
 // What bounds it: with a few weighted trajectories HBM (the gradient's zeros and
-// the source rows). The gradient is written once and not read here, so its
-// stores are non-temporal: T = 10957, D = 8192 (359 MB), 100 trajectories
-// weighted, the whole backward: 148 -> 105 us. (One workgroup a row for the zero
-// rows instead of one per GB_COLS columns: 139 us.) With all of them weighted,
+// the source rows). One workgroup a row for the zero rows instead of one per
+// GB_COLS columns: 139 against 105 us at T = 10957, D = 8192, 100 weighted.
+// A gradient larger than the Infinity Cache is written with non-temporal stores
+// (launch_backward). With all trajectories weighted,
 // the rows that many trajectories have as a neighbour, hundreds of terms long:
 // T = 2000, D = 8192, 1900 of 1996 trajectories weighted, the whole backward:
 // 1424 us with the terms looked up one after the other and one-thread sorts,
@@ -177,8 +177,13 @@ constexpr int GB_BATCH = 4;    // terms whose source vectors are loaded together
 constexpr int GB_REV = 512;    // reverse terms listed at a time
 constexpr int GB_FWD = TRAKNN_MAX_L * TRAKNN_MAX_K;  // forward terms at most
 constexpr int GB_COLS = 256 * 4;
+constexpr uint64_t INFINITY_CACHE_BYTES = (uint64_t)256 << 20;
 
-template <bool VEC_OUT>
+// How the gradient is stored: by element where its rows are not 16-byte aligned,
+// else 16 bytes a lane, through the caches or past them.
+enum GradStore { GRAD_SCALAR, GRAD_VECTOR, GRAD_STREAM };
+
+template <GradStore STORE>
 __global__ __launch_bounds__(256) void grad_rows_kernel(
     const float* __restrict__ X, int64_t ldx, int T, int64_t D, int L, int k,
     const int32_t* __restrict__ idx, const double* __restrict__ w,
@@ -193,8 +198,11 @@ __global__ __launch_bounds__(256) void grad_rows_kernel(
   const int64_t c = (int64_t)blockIdx.y * GB_COLS + 4 * tid;
   float* ga = g + (int64_t)a * ldg;
   auto store = [&](float4 v) __attribute__((always_inline)) {
-    if (VEC_OUT && c + 3 < D) {
-      __builtin_nontemporal_store(f32x4{v.x, v.y, v.z, v.w}, (f32x4*)(ga + c));
+    const f32x4 x = {v.x, v.y, v.z, v.w};
+    if (STORE == GRAD_STREAM && c + 3 < D) {
+      __builtin_nontemporal_store(x, (f32x4*)(ga + c));
+    } else if (STORE == GRAD_VECTOR && c + 3 < D) {
+      *(f32x4*)(ga + c) = x;
     } else {
       if (c < D) ga[c] = v.x;
       if (c + 1 < D) ga[c + 1] = v.y;
@@ -317,12 +325,21 @@ hipError_t launch_backward(const float* X, int64_t ldx, int64_t T, int64_t D,
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const dim3 grid((unsigned)T, (unsigned)((D + GB_COLS - 1) / GB_COLS));
   const bool vec_out = ldg % 4 == 0 && ((uintptr_t)g % 16) == 0;
-  if (vec_out)
-    hipLaunchKernelGGL(grad_rows_kernel<true>, grid, dim3(256), 0, s, X, ldx, (int)T, D, L, k,
-                       idx, w, ptr, rev, touch, g, ldg);
-  else
-    hipLaunchKernelGGL(grad_rows_kernel<false>, grid, dim3(256), 0, s, X, ldx, (int)T, D, L, k,
-                       idx, w, ptr, rev, touch, g, ldg);
+  // Non-temporal stores for a gradient larger than the 256 MB Infinity Cache,
+  // which no reader would find there. D = 8192, 100 trajectories weighted, us
+  // non-temporal / plain. Calls back to back: 133 / 185 (359 MB), 124 / 159 (256
+  // MB), 104 / 113 (192 MB), 72 / 74 (64 MB); one call on an idle GPU: 178 / 168
+  // (359 MB). What counts is the call and a reader of the gradient behind it, on
+  // caches full of other data: 815 / 837 (900 MB), 350 / 356 (300 MB), 328 / 317
+  // (256 MB), 267 / 252 (192 MB), 147 / 128 (64 MB).
+  const bool stream = (uint64_t)T * (uint64_t)D * 4 > INFINITY_CACHE_BYTES;
+#define TRAKNN_GRAD_ROWS(S)                                                                     \
+  hipLaunchKernelGGL(grad_rows_kernel<S>, grid, dim3(256), 0, s, X, ldx, (int)T, D, L, k, idx, \
+                     w, ptr, rev, touch, g, ldg)
+  if (!vec_out) TRAKNN_GRAD_ROWS(GRAD_SCALAR);
+  else if (stream) TRAKNN_GRAD_ROWS(GRAD_STREAM);
+  else TRAKNN_GRAD_ROWS(GRAD_VECTOR);
+#undef TRAKNN_GRAD_ROWS
   return hipGetLastError();
 }
 
