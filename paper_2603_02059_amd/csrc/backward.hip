@@ -162,20 +162,28 @@ __global__ __launch_bounds__(256) void rev_sort_kernel(const int32_t* __restrict
 // rank; W_ba: a = j + m with j in N_t, b = t + m, by m and t -- with the loads
 // of weights, neighbours and reverse lists side by side instead of one behind
 // the other; then each thread gathers its columns in FP64, GB_BATCH terms'
-// source vectors in flight at once, rounded once to FP32.
+// source vectors in flight at once, rounded once to FP32. The first wave lists
+// the forward terms and the first 64 reverse ones, the workgroup the others.
 //
 // What bounds it: with a few weighted trajectories HBM (the gradient's zeros and
 // the source rows). One workgroup a row for the zero rows instead of one per
 // GB_COLS columns: 139 against 105 us at T = 10957, D = 8192, 100 weighted.
 // A gradient larger than the Infinity Cache is written with non-temporal stores
-// (launch_backward). With all trajectories weighted,
-// the rows that many trajectories have as a neighbour, hundreds of terms long:
-// T = 2000, D = 8192, 1900 of 1996 trajectories weighted, the whole backward:
-// 1424 us with the terms looked up one after the other and one-thread sorts,
-// 624 us now.
+// (launch_backward). With all trajectories weighted the source rows, and among
+// them the rows that many trajectories have as a neighbour, hundreds of terms
+// long. T = 2000, D = 8192, L = 5, k = 10, all weighted, the whole backward:
+// 663 us with the terms looked up one after the other and one-thread sorts, 581
+// now; with one trajectory in every list 124 against 1.6 ms.
+//
+// A list costs a short row more than it saves. With one length offset (L = 1)
+// a row's terms are few and lie in two runs, and up to GB_DIRECT of them are
+// read where they are. L = 1, k = 1, all weighted, us looked up / listed /
+// direct: T = 10957, D = 8192 264 / 276 / 243; T = 2000, D = 16384 85 / 89 / 84;
+// T = 20000, D = 512 78 / 82 / 75 (listed by the whole workgroup; by the first
+// wave 266, 90 and 80). 4, 8 and 16 direct terms are within 1% of each other.
 constexpr int GB_BATCH = 4;    // terms whose source vectors are loaded together
-constexpr int GB_REV = 512;    // reverse terms listed at a time
-constexpr int GB_FWD = TRAKNN_MAX_L * TRAKNN_MAX_K;  // forward terms at most
+constexpr int GB_DIRECT = 8;   // most terms of a row of L = 1 that are not listed
+constexpr int GB_REV = 256;    // reverse terms listed at a time, at least 64
 constexpr int GB_COLS = 256 * 4;
 constexpr uint64_t INFINITY_CACHE_BYTES = (uint64_t)256 << 20;
 
@@ -189,8 +197,9 @@ __global__ __launch_bounds__(256) void grad_rows_kernel(
     const int32_t* __restrict__ idx, const double* __restrict__ w,
     const int32_t* __restrict__ ptr, const int32_t* __restrict__ rev,
     const int32_t* __restrict__ touch, float* __restrict__ g, int64_t ldg) {
-  __shared__ double tc[GB_FWD + GB_REV];
-  __shared__ int tb[GB_FWD + GB_REV];
+  extern __shared__ __attribute__((aligned(16))) char terms[];
+  double* const tc = (double*)terms;       // [L k + GB_REV]
+  int* const tb = (int*)(tc + L * k + GB_REV);
   __shared__ int fwd, rv_b[TRAKNN_MAX_L], rv_e[TRAKNN_MAX_L + 1];  // reverse buckets, their ends
   const int a = blockIdx.x;
   const int np = T - L + 1;
@@ -223,12 +232,55 @@ __global__ __launch_bounds__(256) void grad_rows_kernel(
   };
   const double invk = 1.0 / (double)k;
   const float4 x = load(a);
-  if (tid < 64) {  // the first wave lists the forward terms and the buckets
+  const double xa[4] = {x.x, x.y, x.z, x.w};
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  // up to GB_BATCH terms, n of them: term(u, source row, coefficient). The others
+  // read the row itself with weight 0 (an exact zero contribution).
+  auto gather = [&](int n, auto term) __attribute__((always_inline)) {
+    float4 xb[GB_BATCH];
+    double cc[GB_BATCH];
+#pragma unroll
+    for (int u = 0; u < GB_BATCH; ++u) {
+      int b = a;
+      cc[u] = 0.0;
+      if (u < n) term(u, b, cc[u]);
+      xb[u] = load(b);
+    }
+#pragma unroll
+    for (int u = 0; u < GB_BATCH; ++u) {
+      acc[0] += cc[u] * (xa[0] - (double)xb[u].x);
+      acc[1] += cc[u] * (xa[1] - (double)xb[u].y);
+      acc[2] += cc[u] * (xa[2] - (double)xb[u].z);
+      acc[3] += cc[u] * (xa[3] - (double)xb[u].w);
+    }
+  };
+  auto finish = [&]() __attribute__((always_inline)) {
+    store(make_float4((float)(2.0 * acc[0]), (float)(2.0 * acc[1]), (float)(2.0 * acc[2]),
+                      (float)(2.0 * acc[3])));
+  };
+  if (L == 1) {
+    const double wt = w[a];
+    const int nf = wt != 0.0 ? k : 0, p0 = ptr[a], n = nf + ptr[a + 1] - p0;
+    if (n <= GB_DIRECT) {
+      for (int q = 0; q < n; q += GB_BATCH)
+        gather(n - q, [&](int u, int& b, double& c) __attribute__((always_inline)) {
+          const int e = q + u;
+          const int r = e < nf ? idx[(int64_t)a * k + e] : rev[p0 + e - nf];
+          if (e < nf && (r < 0 || r >= np)) return;
+          b = r;
+          c = (e < nf ? wt : w[r]) * invk;
+        });
+      finish();
+      return;
+    }
+  }
+  if (tid < 64) {  // the first wave lists the forward terms and the first reverse ones
+    // the row's weights and reverse buckets, one length offset a lane
     const int ta = a - lane;
     const bool in = lane < L && ta >= 0 && ta < np;
     const double wt = in ? w[ta] : 0.0;
-    const int p0 = in ? ptr[ta] : 0;
-    int sum = in ? ptr[ta + 1] - p0 : 0;
+    const int p0 = in ? ptr[ta] : 0, p1 = in ? ptr[ta + 1] : 0;
+    int sum = p1 - p0;
 #pragma unroll
     for (int o = 1; o < TRAKNN_MAX_L; o <<= 1) {
       const int y = __shfl_up(sum, o, 64);
@@ -239,13 +291,24 @@ __global__ __launch_bounds__(256) void grad_rows_kernel(
       rv_e[lane + 1] = sum;
     }
     if (lane == 0) rv_e[0] = 0;
+    auto neighbour = [&](int m) __attribute__((always_inline)) {
+      return lane < k ? idx[(int64_t)(a - m) * k + lane] : -1;
+    };
     uint64_t ms = __ballot(wt != 0.0);
+    int j = ms ? neighbour(__builtin_ctzll(ms)) : -1;
+    // reverse term `lane`: its bucket rm, its place there
+    int rm = 0;
+    for (int m = 0; m < L; ++m) rm += lane >= __builtin_amdgcn_readlane(sum, m);
+    const bool rev_in = rm < L;
+    const int rp = __shfl(p1 - sum, rev_in ? rm : 0, 64) + lane;
+    const int t = rev_in ? rev[rp] : 0;
+    const double rw = rev_in ? w[t] : 0.0;
     int n = 0;
     while (ms) {
       const int m = __builtin_ctzll(ms);
       ms &= ms - 1;
+      const int jn = ms ? neighbour(__builtin_ctzll(ms)) : -1;
       const double cm = readlane_d(wt, m) * invk;
-      const int j = lane < k ? idx[(int64_t)(a - m) * k + lane] : -1;
       const uint64_t ok = __ballot(j >= 0 && j < np);
       if ((ok >> lane) & 1) {
         const int pos = n + mask_rank(ok);
@@ -253,47 +316,38 @@ __global__ __launch_bounds__(256) void grad_rows_kernel(
         tc[pos] = cm;
       }
       n += __builtin_popcountll(ok);
+      j = jn;
+    }
+    if (rev_in) {
+      tb[n + lane] = t + rm;
+      tc[n + lane] = rw * invk;
     }
     if (lane == 0) fwd = n;
   }
   __syncthreads();
   const int nf = fwd, nr = rv_e[L];
-  const double xa[4] = {x.x, x.y, x.z, x.w};
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
   int done = 0;  // listed terms already gathered (the forward ones, after the first list)
   for (int r0 = 0; r0 == 0 || r0 < nr; r0 += GB_REV) {
     const int n = nf + (nr - r0 < GB_REV ? nr - r0 : GB_REV);
     if (r0 > 0) __syncthreads();  // the previous list is used
-    for (int e = tid; e < n - nf; e += 256) {
-      int m = 0;
-      while (r0 + e >= rv_e[m + 1]) ++m;
-      const int t = rev[rv_b[m] + (r0 + e - rv_e[m])];
-      tb[nf + e] = t + m;
-      tc[nf + e] = w[t] * invk;
-    }
-    __syncthreads();
-    // unused entries of a batch read the row itself with weight 0 (an exact
-    // zero contribution)
-    for (int q = done; q < n; q += GB_BATCH) {
-      float4 xb[GB_BATCH];
-      double cc[GB_BATCH];
-#pragma unroll
-      for (int u = 0; u < GB_BATCH; ++u) {
-        xb[u] = load(q + u < n ? tb[q + u] : a);
-        cc[u] = q + u < n ? tc[q + u] : 0.0;
+    if (nr > 64) {  // the first 64 are listed
+      for (int e = r0 > 0 ? tid : tid + 64; e < n - nf; e += 256) {
+        int m = 0;
+        while (r0 + e >= rv_e[m + 1]) ++m;
+        const int t = rev[rv_b[m] + (r0 + e - rv_e[m])];
+        tb[nf + e] = t + m;
+        tc[nf + e] = w[t] * invk;
       }
-#pragma unroll
-      for (int u = 0; u < GB_BATCH; ++u) {
-        acc[0] += cc[u] * (xa[0] - (double)xb[u].x);
-        acc[1] += cc[u] * (xa[1] - (double)xb[u].y);
-        acc[2] += cc[u] * (xa[2] - (double)xb[u].z);
-        acc[3] += cc[u] * (xa[3] - (double)xb[u].w);
-      }
+      __syncthreads();
     }
+    for (int q = done; q < n; q += GB_BATCH)
+      gather(n - q, [&](int u, int& b, double& c) __attribute__((always_inline)) {
+        b = tb[q + u];
+        c = tc[q + u];
+      });
     done = nf;
   }
-  store(make_float4((float)(2.0 * acc[0]), (float)(2.0 * acc[1]), (float)(2.0 * acc[2]),
-                    (float)(2.0 * acc[3])));
+  finish();
 }
 
 }  // namespace
@@ -324,6 +378,7 @@ hipError_t launch_backward(const float* X, int64_t ldx, int64_t T, int64_t D,
   hipLaunchKernelGGL(rev_sort_kernel, dim3((unsigned)((np + 3) / 4)), dim3(256), 0, s, ptr, np, rev);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const dim3 grid((unsigned)T, (unsigned)((D + GB_COLS - 1) / GB_COLS));
+  const size_t lds = (size_t)(L * k + GB_REV) * (sizeof(double) + sizeof(int));  // at most 15 KB
   const bool vec_out = ldg % 4 == 0 && ((uintptr_t)g % 16) == 0;
   // Non-temporal stores for a gradient larger than the 256 MB Infinity Cache,
   // which no reader would find there. D = 8192, 100 trajectories weighted, us
@@ -334,7 +389,7 @@ hipError_t launch_backward(const float* X, int64_t ldx, int64_t T, int64_t D,
   // (256 MB), 267 / 252 (192 MB), 147 / 128 (64 MB).
   const bool stream = (uint64_t)T * (uint64_t)D * 4 > INFINITY_CACHE_BYTES;
 #define TRAKNN_GRAD_ROWS(S)                                                                     \
-  hipLaunchKernelGGL(grad_rows_kernel<S>, grid, dim3(256), 0, s, X, ldx, (int)T, D, L, k, idx, \
+  hipLaunchKernelGGL(grad_rows_kernel<S>, grid, dim3(256), lds, s, X, ldx, (int)T, D, L, k, idx, \
                      w, ptr, rev, touch, g, ldg)
   if (!vec_out) TRAKNN_GRAD_ROWS(GRAD_SCALAR);
   else if (stream) TRAKNN_GRAD_ROWS(GRAD_STREAM);
