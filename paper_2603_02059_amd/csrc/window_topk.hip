@@ -550,19 +550,24 @@ __global__ __launch_bounds__(256) void score_prefix_kernel(
 //
 // Bound by the FP64 logarithms, k (k - 1) / 2 a row: the thread of (row, i)
 // takes the ranks q = i and q = k - 1 - i, k - 1 logarithms in all, so that
-// every lane has the same number. T = 27394, k = 40: 280 us with one thread per
-// row (107 workgroups), 140 with one per (row, q), 95 now.
+// every lane has the same number. T = 27394, k = 40: 260 us with one thread per
+// row (107 workgroups), 140 with one per (row, q), 82 now; k = 10: 18 and 9 us.
+// With hundreds of thousands of rows and k up to 5 a thread per row was as fast
+// (ten lengths, k = 3: 7.0 against 7.9 us, k = 5: 15.3 and 16.6, k = 7: 30.9 and
+// 27.3).
 __global__ __launch_bounds__(256) void local_dim_kernel(
     const double* __restrict__ dist, int T, int np0, int Lmin, int NL, int k,
     double* __restrict__ out) {
-  const int half = (k + 1) / 2;
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= (int64_t)NL * np0 * half) return;
-  const int64_t g = e / half;
-  const int lo = (int)(e % half), hi = k - 1 - lo;
-  const int li = (int)(g / np0);
-  const int t = (int)(g % np0);
+  // at most 16 lengths x 2^20 rows x 32 pairs of ranks: 32 bits hold them
+  const unsigned half = (unsigned)(k + 1) / 2;
+  const unsigned e = blockIdx.x * 256u + threadIdx.x;
+  if (e >= (unsigned)NL * (unsigned)np0 * half) return;
+  const unsigned row = e / half;
+  const int lo = (int)(e - row * half), hi = k - 1 - lo;
+  const int li = (int)(row / (unsigned)np0);
+  const int t = (int)(row - (unsigned)li * (unsigned)np0);
   const bool exists = t < T - (Lmin + li) + 1;
+  const int64_t g = row;
   const double* d = dist + g * k;
   const double d_lo = d[lo], d_hi = d[hi];
   double s_lo = 0.0, s_hi = 0.0;
