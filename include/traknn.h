@@ -176,9 +176,8 @@ typedef struct traknn_plan_s* traknn_plan_t;
  *                          and traknn_score_backward (one size covers both).
  * Errors: INVALID_ARG for NULL pointers, sizes out of range or a row_batch that
  * is negative or not a multiple of 8; UNSUPPORTED for a multi-length sweep with
- * L_min != 1, or a D whose 256-field
- * Gram operand panel would reach 2 GiB (D >= 2^21 for FP32 and BF16X3,
- * D >= 2^22 for FP16). */
+ * L_min != 1, or a D at which 256 fields of the Gram's operand would reach 2 GiB
+ * (D >= 2^21 for FP32 and BF16X3, D >= 2^22 for FP16). */
 int traknn_plan(const traknn_config* cfg, traknn_plan_t* out,
                 size_t* workspace_bytes);
 

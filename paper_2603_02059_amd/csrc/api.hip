@@ -32,11 +32,12 @@ bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 int fail_hip(hipError_t e) { return e == hipSuccess ? TRAKNN_OK : TRAKNN_ERR_HIP; }
 
 // The size of the workspace's spare region, in lists per row, for `rows` rows
-// over `cands` candidate columns. The window stage once kept that many partial
-// lists of every row there; it writes its lists to the output now. The region
-// stays in the workspace so that a plan's workspace_bytes, and with them which
-// plans traknn_knn_noalloc accepts and which row_batch fits a budget, do not
-// change.
+// over `cands` candidate columns. No kernel reads or writes the region: partial
+// lists of the window stage lay there, whose numbers this formula gave, and the
+// window writes its lists to the output now. The region stays so that
+// workspace_bytes, which plans traknn_knn_noalloc accepts and which row_batch
+// fits a budget remain what callers have. It costs them memory only: 13 MB at T =
+// 27394, k = 10, tens of MB for ten lengths.
 int spare_lists(const traknn_plan_s* p, int64_t rows, int64_t cands, int64_t target) {
   const int64_t k = p->cfg.k, G = p->NL > 1 ? 2 : 1;
   const int64_t base = G * 64, per = (int64_t)(p->cfg.L_max + 15) * 256 + G * 96 * k;
@@ -59,7 +60,7 @@ void plan_fused(traknn_plan_s* p) {
   g.L = c.L_max;
   g.k = c.k;
   g.B = tile - (c.L_max - 1);
-  if (!f64) g.B = g.B / 4 * 4;  // 16-byte aligned chunk-norm loads of each panel
+  if (!f64) g.B = g.B / 4 * 4;  // even: the consumer takes a tile in two halves of B / 2
   g.nbt = (int)((g.np + g.B - 1) / g.B);
   g.blo = g.bhi = 0;
   // Round ends: each launch's last wave of tiles is partly idle, so the
@@ -104,11 +105,15 @@ void plan_fused(traknn_plan_s* p) {
 }
 
 // Band passes: the starts t0 of passes of at most rb rows, on multiples of 8
-// (the chunk-norm loads' alignment). Each pass's Gram launch ends with a
-// partly idle round of 256 tiles, so the starts minimise, by dynamic
-// programming from the last row back, the passes' rounds plus lambda rounds
-// per pass: a pass's own windows and merge cost about the same at any D,
-// while a round of tiles grows with D, so lambda = 1 + 8192 / Dpad. A pass of
+// (the window's row blocks then start where the whole matrix's do). Each pass's
+// Gram launch ends with a partly idle round of 256 tiles, so the starts
+// minimise, by dynamic programming from the last row back, the passes' rounds
+// plus lambda rounds per pass: a pass's own windows cost about the same at any
+// D, while a round of tiles grows with D, so lambda = 1 + 8192 / Dpad. The rounds
+// are counted in 256-field tiles, also where the launch takes smaller ones
+// (pick_tile), which it does for short passes, whose last round is then less
+// idle than counted here; lambda was fitted when each pass also merged lists. So
+// the starts are not tuned to the present launches. A pass of
 // nt rows from t0 covers nbi = ceil((nt + L_max - 1) / 256) block-rows against
 // the block-columns from t0 / 256 on; for each nbi only the longest such pass
 // is tried, and only the 16 largest nbi (all of them up to passes of 4096
@@ -441,10 +446,12 @@ int traknn_plan(const traknn_config* cfg, traknn_plan_t* out,
   // every row of every length needs k candidates outside its exclusion zone
   if (c.T - c.L_max + 1 < (int64_t)c.k + 2 * c.L_max - 1)
     return TRAKNN_ERR_INVALID_ARG;
-  // band mode: passes start on multiples of 8 rows (16-byte aligned norm loads)
+  // band mode: passes start on multiples of 8 rows (the window's row blocks)
   if (c.row_batch < 0 || c.row_batch % 8 != 0) return TRAKNN_ERR_INVALID_ARG;
   if (c.L_min != c.L_max && c.L_min != 1) return TRAKNN_ERR_UNSUPPORTED;
-  // the Gram stage addresses a 256-field operand panel with 32-bit offsets
+  // 256 rows of the operand in less than 2 GiB: what has been run. The Gram stage
+  // addressed such a panel with 32-bit offsets; it addresses a 64-byte slice of it
+  // now, and no kernel is known to need the limit
   if ((uint64_t)round_up(c.D, stage_k(c.precision)) * elem_bytes(c.precision) * GRAM_TILE >
       0x7FFFFFFFull)
     return TRAKNN_ERR_UNSUPPORTED;

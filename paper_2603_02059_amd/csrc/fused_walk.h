@@ -356,12 +356,17 @@ __device__ __forceinline__ int recipient_establish(const float* V, int sp, int s
 // an LDS counter, unsorted; a recipient with more than k of them is left to
 // filter_overflow. So a pair is read and summed once for both sides, and what a
 // recipient costs by itself is one counter, where side_topk reads every pair L
-// times for either side with a wave per recipient. Calls in FP64 at T = 27394,
-// L = 5, side_topk -> scan_part: D = 13, k = 40 1.78 -> 1.59 ms; D = 33, k = 10
-// 2.34 -> 2.22 ms. With few places per slot (k = 3: 0.43 -> 0.45 ms at T =
-// 12000) the recipients that overflow take the gain back, hence SCAN_MIN_K. The
-// MFMA consumer keeps side_topk: it would have to stage the columns that
-// overflow (L = 12, k = 10, T = 12000 in FP16: 0.79 -> 0.91 ms).
+// times for either side with a wave per recipient. So it gains more the longer the
+// trajectories are; with few places per slot (k = 3: 0.43 -> 0.45 ms at T = 12000)
+// the recipients that overflow take the gain back, hence SCAN_MIN_K. Calls in FP64
+// by side_topk and by scan_part, us: T = 20000, D = 13, k = 8: L = 1 658 and 647,
+// L = 5 747 and 665, L = 9 836 and 722, L = 16 1102 and 873; k = 64: L = 1 1812 and
+// 1788, L = 16 2206 and 1845. T = 6000, k = 8: L = 1 156 and 163, L = 5 179 and 172,
+// L = 16 241 and 218. T = 1500: within 7% either way, the scan ahead from L = 5 on.
+// Where all distances tie, every recipient overflows (a constant series, T = 4000,
+// L = 5, k = 40: 281 and 323). The MFMA consumer keeps side_topk: it would have to
+// stage the columns that overflow (L = 12, k = 10, T = 12000 in FP16: 0.79 -> 0.91
+// ms).
 constexpr int SCAN_MIN_K = 8;
 constexpr int SCAN_ROWS = 4;
 constexpr int SCAN_PAD = SCAN_ROWS;  // floats a staged part has to itself either side

@@ -82,8 +82,8 @@ struct GramShape {
   static_assert((BUFFERS & (BUFFERS - 1)) == 0 && BUFFERS >= 4, "buffers: a power of two");
 };
 // 256: large problems and the fused mode. 128 and 64: launches that would leave
-// CUs idle (pick_tile); two and up to four of their workgroups share a CU, and
-// the 64-field tile, whose steps are the shortest, keeps eight slices in
+// CUs idle (pick_tile); two workgroups of either share a CU (66 KB of LDS each),
+// and the 64-field tile, whose steps are the shortest, keeps eight slices in
 // flight.
 using Shape256 = GramShape<GRAM_TILE, GRAM_THREADS, 4>;
 using Shape128 = GramShape<128, 256, 4>;

@@ -67,8 +67,10 @@ constexpr int FUSED_ROUNDS = 4;
 // stride B, and their consumer skips its test.
 constexpr int FUSED_FIRST_END = 2;
 static_assert(FUSED_FIRST_END >= 2, "the first round covers tile offsets 0 and 1");
-// Ends of the second and third rounds: by default 8 and 32; the planner moves
-// them within [6, 12] and [24, 48] to fill the launches' last waves of tiles.
+// Ends of the second and third rounds: the planner searches [6, 12] and [24, 48]
+// for those that fill the launches' last waves of tiles best; these are taken
+// where no other pair needs fewer waves (twice as much throughout for the FP64
+// tiles).
 constexpr int FUSED_END_DEFAULT[2] = {12, 48};
 // Compute units of an MI355X: the tiles resident at once are this many times
 // the workgroups of a fused tile kernel per CU (1 MFMA, 2 FP64).
@@ -138,7 +140,7 @@ hipError_t launch_centre_convert(const float* X, int64_t ldx, int64_t T,
                                  int precision, int parts, const double* mu, void* xc,
                                  float* ncs, hipStream_t s);
 // Up to this many blocks of partial sums are added by every wave of the
-// centring itself (32 KB of reads a wave at most), which saves a short series
+// centring itself (16 KB of reads a wave at most), which saves a short series
 // the reduction's launch.
 constexpr int INLINE_PARTS = 4;
 // gram.hip

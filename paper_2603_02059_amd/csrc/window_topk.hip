@@ -47,9 +47,10 @@ namespace {
 // Window + top-k kernel for the trajectory lengths L .. L + G - 1.
 //
 // What bounds it: one length at T = 27394 reads 4.7 GB of S (both triangles and
-// the L - 1 halo rows of every eight) in 0.69 ms (L = 5, k = 10; 0.82 ms at k =
-// 40), at the rate of a large read; short series, the latency of a few rounds
-// (12 us at T = 512, 52 us at T = 5000); several lengths, vector issue. Before,
+// the L - 1 halo rows of every eight) in 0.69 to 0.76 ms (L = 5, k = 10; 0.82 to
+// 1.0 ms at k = 40; box to box, and under the clocks of the Gram before it), at
+// the rate of a large read; short series, the latency of a few rounds (12 us at T
+// = 512, 52 us at T = 5000); several lengths, vector issue. Before,
 // every wave kept a list of its own for each of the eight rows and a merge
 // kernel joined them, so that the work on lists grew with the waves: 0.84 and
 // 1.39 ms plus 0.02 and 0.03 of merge at T = 27394, 28 + 14 us at T = 512, 125 +
@@ -77,8 +78,11 @@ namespace {
 // round is taken densely: the waves put all their sums in LDS, and each owner
 // picks from its row's 512. It bounds them first by the k-th smallest of its
 // lanes' minima (at least k are within it), so that one sort of at most 64 is
-// the usual cost. Which rounds are dense changes nothing in the lists: they hold
-// the k smallest of all candidates by (distance, index).
+// the usual cost. Where distances fall along the scan every round is dense, and
+// still cheaper than one insertion per candidate was: a ramp of T = 8000, D = 64,
+// whole calls, L = 5, k = 10 1396 -> 711 us, L = 16, k = 64 5568 -> 2725; T = 5000,
+// L = 1..10, k = 5 7660 -> 3135. Which rounds are dense changes nothing in the
+// lists: they hold the k smallest of all candidates by (distance, index).
 //
 // A launch may start from lists that are already in the output (band mode's
 // later passes): their rows have a bound from the first round on.
